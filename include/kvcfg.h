@@ -287,8 +287,8 @@ kv_status kv_eval_configs(const kv_trace* t, const kv_config* cfg, uint32_t n_cf
  *             stores the number of flagged rows
  * A row with a NaN objective is never on the front and never dominates.
  * Without n_front the call is asynchronous and cannot report a NaN: such rows
- * simply get flag 0 and dominate nothing.  Calls on different streams of one
- * device take turns (they share the device's result counters).
+ * simply get flag 0 and dominate nothing.  Calls with n_front on different
+ * streams of one device take turns (they share the device's result words).
  * Errors: KV_ERR_INVALID for NULL obj/on_front with n > 0, or n > 2^26; when
  * n_front is non-NULL, also KV_ERR_INVALID if any objective is NaN (flags are
  * still written).  n == 0 is a no-op (n_front = 0). */

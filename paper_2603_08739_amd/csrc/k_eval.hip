@@ -256,81 +256,187 @@ __device__ __forceinline__ bool feasible(double o0, double o1, double o2, const 
   return true;
 }
 
-// Flag of every point: 1 if it meets the bounds (and has no NaN), else 0;
-// the NaN flag of the call.
-__global__ __launch_bounds__(256) void k_pareto_init(const double* __restrict__ obj, uint32_t n,
-                                                     Bounds bd, uint8_t* __restrict__ flag,
-                                                     uint32_t* __restrict__ counters) {
-  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
-  if (b >= n) return;
-  const double o0 = obj[3 * (uint64_t)b], o1 = obj[3 * (uint64_t)b + 1],
-               o2 = obj[3 * (uint64_t)b + 2];
-  flag[b] = feasible(o0, o1, o2, bd) ? 1 : 0;
-  if (o0 != o0 || o1 != o1 || o2 != o2) atomicOr(&counters[1], 1u);
+// a dominates b, both of one segment.
+__device__ __forceinline__ bool dominates(double a0, double a1, double a2, double b0, double b1,
+                                          double b2) {
+  return a0 <= b0 && a1 >= b1 && a2 <= b2 && (a0 < b0 || a1 > b1 || a2 < b2);
 }
 
-// All-pairs dominance over a grid of (points, candidates) tiles: block
-// (x, y) tests points [256 x, 256 x + 256) against the feasible candidates
-// of its slice [y * per, (y + 1) * per), staged through LDS 256 at a time,
-// and clears the flag of every point a candidate of its segment dominates.
-// Every writer stores 0, so the blocks need no ordering; the result is the
-// same whichever candidates a block sees as still flagged, as dominance is
-// transitive (only the objectives and the bounds decide a candidate).
-__global__ __launch_bounds__(256) void k_pareto(const double* __restrict__ obj,
-                                                const uint32_t* __restrict__ seg, uint32_t n,
-                                                uint32_t per, Bounds bd, uint8_t* __restrict__ flag) {
-  __shared__ double so[3][256];
-  __shared__ uint32_t ss[256];
-  __shared__ uint32_t sf[256];
-  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
-  double ob0 = 0, ob1 = 0, ob2 = 0;
+__device__ __forceinline__ double lane_f64(double v, int lane) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(v), lane);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(v), lane);
+  return __hiloint2double(hi, lo);
+}
+
+constexpr int kPaNT = 256;  // points of a tile, one thread each
+
+// A tile's points that may still be on the front, packed.
+struct PaTile {
+  double o[3][kPaNT];
+  uint32_t seg[kPaNT];
+  uint32_t idx[kPaNT];  // row
+  uint32_t dom[kPaNT];  // found dominated
+  uint32_t wsum[kPaNT / 64];
+  uint32_t n;
+};
+
+// Packs the rows of the threads with `keep` into t (any earlier reader of t
+// is past a barrier).  Two barriers.
+__device__ __forceinline__ void pa_pack(PaTile& t, bool keep, uint32_t row, uint32_t seg, double o0,
+                                        double o1, double o2) {
+  const uint64_t m = __ballot(keep);
+  const int w = wave_id();
+  if (lane_id() == 0) t.wsum[w] = (uint32_t)__popcll(m);
+  __syncthreads();
+  uint32_t at = 0, all = 0;
+#pragma unroll
+  for (int i = 0; i < kPaNT / 64; ++i) {
+    if (i < w) at += t.wsum[i];
+    all += t.wsum[i];
+  }
+  at += (uint32_t)__popcll(m & lanemask_lt());
+  if (keep) {
+    t.o[0][at] = o0;
+    t.o[1][at] = o1;
+    t.o[2][at] = o2;
+    t.seg[at] = seg;
+    t.idx[at] = row;
+    t.dom[at] = 0;
+  }
+  if (threadIdx.x == 0) t.n = all;
+  __syncthreads();
+}
+
+// Marks the points of `p` that a candidate of `c` dominates.  With few
+// points, k threads share one point's candidates, so the block stays busy.
+__device__ __forceinline__ void pa_compare(PaTile& p, const PaTile& c) {
+  const uint32_t np = p.n, nc = c.n;
+  uint32_t k = 1;
+  while (2 * k * np <= (uint32_t)kPaNT && k < 64) k *= 2;
+  const uint32_t i = threadIdx.x / k;
+  if (i >= np || p.dom[i]) return;
+  const double b0 = p.o[0][i], b1 = p.o[1][i], b2 = p.o[2][i];
+  const uint32_t sb = p.seg[i];
+  for (uint32_t j = threadIdx.x % k; j < nc; j += k) {
+    if (c.seg[j] == sb && dominates(c.o[0][j], c.o[1][j], c.o[2][j], b0, b1, b2)) {
+      p.dom[i] = 1;
+      break;
+    }
+  }
+}
+
+// Flag of every point: 1 if it meets the bounds (and has no NaN) and no
+// other such point of its tile of 256 and its segment dominates it.  First
+// each wavefront's 64 points against each other, the candidate broadcast
+// from a lane, then the tile's remaining points against each other.  With
+// one tile (n <= 256) that is the front, and `result` (or null) receives
+// {flagged rows, NaN seen}; with more, a NaN sets *nan_seen (or null).
+// Comparisons bound this filter, and a point dominated inside its tile need
+// not be compared with the other tiles' points at all.  A call over 11,000
+// sweep objectives takes 53 us (163 us with all pairs in one pass, whose
+// kernel ran 141 us); for 512 points, whose two tiles left the chip idle
+// for 66 us, the whole load-and-evaluate step shortens by 92 us.
+__global__ __launch_bounds__(kPaNT) void k_pareto_tile(const double* __restrict__ obj,
+                                                       const uint32_t* __restrict__ seg, uint32_t n,
+                                                       Bounds bd, uint8_t* __restrict__ flag,
+                                                       uint32_t* __restrict__ nan_seen,
+                                                       uint32_t* __restrict__ result) {
+  __shared__ PaTile t;
+  __shared__ uint32_t left[kPaNT / 64], bad[kPaNT / 64];
+  const uint32_t b = blockIdx.x * kPaNT + threadIdx.x;
+  double o0 = 0, o1 = 0, o2 = 0;
   uint32_t sb = 0;
-  bool live = false;
-  if (b < n && flag[b]) {
-    ob0 = obj[3 * (uint64_t)b];
-    ob1 = obj[3 * (uint64_t)b + 1];
-    ob2 = obj[3 * (uint64_t)b + 2];
+  bool live = false, nan = false;
+  if (b < n) {
+    o0 = obj[3 * (uint64_t)b];
+    o1 = obj[3 * (uint64_t)b + 1];
+    o2 = obj[3 * (uint64_t)b + 2];
     sb = seg ? seg[b] : 0u;
-    live = true;
+    live = feasible(o0, o1, o2, bd);
+    nan = o0 != o0 || o1 != o1 || o2 != o2;
   }
-  const uint32_t c0 = blockIdx.y * per, c1 = min(n, c0 + per);
+  const uint64_t any_nan = __ballot(nan);
+  const uint64_t cand = __ballot(live);
   bool dom = false;
-  for (uint32_t a0 = c0; a0 < c1; a0 += 256) {
-    const uint32_t a = a0 + threadIdx.x;
-    if (a < c1) {
-      const double x0 = obj[3 * (uint64_t)a], x1 = obj[3 * (uint64_t)a + 1],
-                   x2 = obj[3 * (uint64_t)a + 2];
-      so[0][threadIdx.x] = x0;
-      so[1][threadIdx.x] = x1;
-      so[2][threadIdx.x] = x2;
-      ss[threadIdx.x] = seg ? seg[a] : 0u;
-      sf[threadIdx.x] = feasible(x0, x1, x2, bd) ? 1u : 0u;
-    }
-    __syncthreads();
-    const uint32_t m = min(256u, c1 - a0);
-    if (live && !dom) {
-      for (uint32_t j = 0; j < m; ++j) {
-        if (a0 + j == b || !sf[j] || ss[j] != sb) continue;
-        const double x0 = so[0][j], x1 = so[1][j], x2 = so[2][j];
-        const bool le = x0 <= ob0 && x1 >= ob1 && x2 <= ob2;
-        const bool lt = x0 < ob0 || x1 > ob1 || x2 < ob2;
-        if (le && lt) {
-          dom = true;
-          break;
-        }
-      }
-    }
-    __syncthreads();
+  for (uint64_t left_c = cand; left_c; left_c &= left_c - 1) {
+    const int j = (int)__builtin_ctzll(left_c);
+    const double a0 = lane_f64(o0, j), a1 = lane_f64(o1, j), a2 = lane_f64(o2, j);
+    const uint32_t sa = (uint32_t)__builtin_amdgcn_readlane((int)sb, j);
+    dom |= sa == sb && dominates(a0, a1, a2, o0, o1, o2);
   }
-  if (dom) flag[b] = 0;
+  live = live && !dom;
+  if (b < n && !live) flag[b] = 0;
+  pa_pack(t, live, b, sb, o0, o1, o2);
+  pa_compare(t, t);
+  __syncthreads();
+  const bool on = threadIdx.x < t.n && !t.dom[threadIdx.x];
+  if (threadIdx.x < t.n) flag[t.idx[threadIdx.x]] = on ? 1 : 0;
+  if (nan_seen && any_nan && lane_id() == 0) atomicOr(nan_seen, 1u);
+  if (result) {
+    const uint64_t m = __ballot(on);
+    if (lane_id() == 0) {
+      left[wave_id()] = (uint32_t)__popcll(m);
+      bad[wave_id()] = any_nan != 0;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      result[0] = left[0] + left[1] + left[2] + left[3];
+      result[1] = bad[0] | bad[1] | bad[2] | bad[3];
+    }
+  }
 }
 
-// Points left on the front.
-__global__ __launch_bounds__(256) void k_pareto_count(const uint8_t* __restrict__ flag, uint32_t n,
-                                                      uint32_t* __restrict__ counters) {
-  const uint32_t b = blockIdx.x * 256 + threadIdx.x;
-  const uint64_t on = __ballot(b < n && flag[b]);
-  if ((threadIdx.x & 63) == 0 && on) atomicAdd(&counters[0], (uint32_t)__popcll(on));
+// Dominance between tiles over a grid of (point tile, candidate slice):
+// block (x, y) tests the points of tile x still flagged against the points
+// still flagged in tiles [y * per, (y + 1) * per) and clears the flag of
+// every point a candidate dominates.  Every writer stores 0, so the blocks
+// need no ordering; whichever flags a block still sees set, the result is the
+// same: dominance is transitive, so a point dominated by a cleared candidate
+// is dominated by the one that cleared it or one that never is.
+__global__ __launch_bounds__(kPaNT) void k_pareto_cross(const double* __restrict__ obj,
+                                                        const uint32_t* __restrict__ seg,
+                                                        uint32_t n, uint32_t per, uint8_t* flag) {
+  __shared__ PaTile p, c;
+  auto pack = [&](PaTile& t, uint32_t tile) {
+    const uint32_t b = tile * kPaNT + threadIdx.x;
+    const bool keep = b < n && flag[b];
+    double o0 = 0, o1 = 0, o2 = 0;
+    uint32_t sb = 0;
+    if (keep) {
+      o0 = obj[3 * (uint64_t)b];
+      o1 = obj[3 * (uint64_t)b + 1];
+      o2 = obj[3 * (uint64_t)b + 2];
+      sb = seg ? seg[b] : 0u;
+    }
+    pa_pack(t, keep, b, sb, o0, o1, o2);
+  };
+  pack(p, blockIdx.x);
+  if (p.n == 0) return;
+  const uint32_t tiles = (n + kPaNT - 1) / kPaNT;
+  const uint32_t t1 = min(tiles, (blockIdx.y + 1) * per);
+  for (uint32_t t = blockIdx.y * per; t < t1; ++t) {
+    if (t == blockIdx.x) continue;  // its own pairs are settled
+    pack(c, t);
+    pa_compare(p, c);
+    __syncthreads();
+  }
+  if (threadIdx.x < p.n && p.dom[threadIdx.x]) flag[p.idx[threadIdx.x]] = 0;
+}
+
+// {points left on the front, NaN seen} into `result`, by one block; *nan_seen
+// is cleared for the next call.
+__global__ __launch_bounds__(1024) void k_pareto_count(const uint8_t* __restrict__ flag, uint32_t n,
+                                                       uint32_t* __restrict__ nan_seen,
+                                                       uint32_t* __restrict__ result) {
+  __shared__ uint32_t sh[16];
+  uint32_t v = 0;
+  for (uint32_t i = threadIdx.x; i < n; i += 1024) v += flag[i];
+  v = block_sum<1024>(v, sh);
+  if (threadIdx.x == 0) {
+    result[0] = v;
+    result[1] = *nan_seen;
+    *nan_seen = 0;
+  }
 }
 
 }  // namespace
@@ -367,22 +473,27 @@ kv_status objectives(const kv_config* cfg_dev, uint32_t n_cfg, uint32_t n_groups
 }
 
 kv_status pareto(const double* obj, const uint32_t* segment, uint32_t n, const double* bounds,
-                 uint8_t* flag, uint32_t* counters_dev, hipStream_t s) {
+                 uint8_t* flag, uint32_t* nan_seen, uint32_t* result, hipStream_t s) {
   const double nan = __builtin_nan("");
   Bounds bd{bounds ? bounds[0] : nan, bounds ? bounds[1] : nan, bounds ? bounds[2] : nan};
   StageTimer tm(kStPareto, s);
   if (n == 0) return KV_OK;
-  // point tiles x candidate slices: about 2,048 blocks, slices of whole tiles
-  const uint32_t nt = div_up(n, 256);
+  const uint32_t nt = div_up(n, kPaNT);
+  hipLaunchKernelGGL(k_pareto_tile, dim3(nt), dim3(kPaNT), 0, s, obj, segment, n, bd, flag,
+                     nt > 1 && result ? nan_seen : (uint32_t*)nullptr,
+                     nt == 1 ? result : (uint32_t*)nullptr);
+  KV_HIP(hipGetLastError());
+  if (nt == 1) return KV_OK;
+  // point tiles x candidate slices: about 2,048 blocks, eight to a compute unit
   const uint32_t ny = std::max<uint32_t>(1, std::min<uint32_t>(nt, div_up(2048, nt)));
-  const uint32_t per = div_up(nt, ny) * 256;
-  hipLaunchKernelGGL(k_pareto_init, dim3(nt), dim3(256), 0, s, obj, n, bd, flag, counters_dev);
+  const uint32_t per = div_up(nt, ny);
+  hipLaunchKernelGGL(k_pareto_cross, dim3(nt, div_up(nt, per)), dim3(kPaNT), 0, s, obj, segment, n,
+                     per, flag);
   KV_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_pareto, dim3(nt, div_up(n, per)), dim3(256), 0, s, obj, segment, n, per,
-                     bd, flag);
-  KV_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_pareto_count, dim3(nt), dim3(256), 0, s, flag, n, counters_dev);
-  KV_HIP(hipGetLastError());
+  if (result) {
+    hipLaunchKernelGGL(k_pareto_count, dim3(1), dim3(1024), 0, s, flag, n, nan_seen, result);
+    KV_HIP(hipGetLastError());
+  }
   return KV_OK;
 }
 

@@ -445,12 +445,15 @@ kv_status run_stack(Trace& t, Order& o, bool partitioned, ThresholdSet& ts, Stac
   return KV_OK;
 }
 
-// kv_pareto's device counters, one set per device, kept until the process
-// ends; `done` is recorded after each call's last use of them.
+// What kv_pareto's counting calls share, one set per device, kept until the
+// process ends: a NaN flag on the device (zero between calls) and the pinned
+// host words the device writes the result to; `done` is recorded after each
+// call's last use of them.
 struct PareCounters {
   std::mutex mu;
   DevBuf buf;
-  uint32_t* host = nullptr;  // pinned
+  uint32_t* host = nullptr;   // pinned
+  uint32_t* host_dev = nullptr;  // the same words by their device address
   hipEvent_t done = nullptr;
 };
 
@@ -463,12 +466,14 @@ kv_status pareto_counters(PareCounters** out) {
   std::lock_guard<std::mutex> lk(mu);
   if (!per_dev[d]) {
     auto* pc = new PareCounters();
-    kv_status st = pc->buf.reserve(2 * sizeof(uint32_t));
+    kv_status st = pc->buf.reserve(sizeof(uint32_t));
+    if (st == KV_OK) st = fill_u32(pc->buf.as<uint32_t>(), 0, 1, nullptr);
     if (st != KV_OK) {
       delete pc;
       return st;
     }
     hipError_t e = hipHostMalloc((void**)&pc->host, 2 * sizeof(uint32_t), hipHostMallocDefault);
+    if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&pc->host_dev, pc->host, 0);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&pc->done, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventRecord(pc->done, nullptr);
     if (e != hipSuccess) {
@@ -814,28 +819,20 @@ kv_status kv_pareto(const double* obj, const uint32_t* segment, uint32_t n, cons
   if (!obj || !on_front) return fail(KV_ERR_INVALID, "kv_pareto: obj and on_front are required");
   if (n > (1u << 26)) return fail(KV_ERR_INVALID, "kv_pareto: n must be <= 2^26");
   hipStream_t s = (hipStream_t)stream;
-  // the per-device counters {flagged rows, NaN seen}, allocated on the first
-  // call; calls on different streams take turns through `done`
+  if (!n_front) return pareto(obj, segment, n, bounds, on_front, nullptr, nullptr, s);
+  // the device's result words, allocated on the first call; calls on
+  // different streams take turns through `done`
   PareCounters* pc = nullptr;
   kv_status st = pareto_counters(&pc);
   if (st != KV_OK) return st;
   std::lock_guard<std::mutex> lk(pc->mu);
   KV_HIP(hipStreamWaitEvent(s, pc->done, 0));
-  uint32_t* counters = pc->buf.as<uint32_t>();
-  st = fill_u32(counters, 0, 2, s);
-  if (st == KV_OK) st = pareto(obj, segment, n, bounds, on_front, counters, s);
-  if (st == KV_OK && n_front) {
-    hipError_t e = hipMemcpyAsync(pc->host, counters, 2 * sizeof(uint32_t),
-                                  hipMemcpyDeviceToHost, s);
-    if (e != hipSuccess) st = hip_fail(e, "kv_pareto result copy");
-  }
+  st = pareto(obj, segment, n, bounds, on_front, pc->buf.as<uint32_t>(), pc->host_dev, s);
   KV_HIP(hipEventRecord(pc->done, s));
   if (st != KV_OK) return st;
-  if (n_front) {
-    KV_HIP(hipEventSynchronize(pc->done));
-    *n_front = pc->host[0];
-    if (pc->host[1]) return fail(KV_ERR_INVALID, "kv_pareto: an objective is NaN");
-  }
+  KV_HIP(hipEventSynchronize(pc->done));
+  *n_front = pc->host[0];
+  if (pc->host[1]) return fail(KV_ERR_INVALID, "kv_pareto: an objective is NaN");
   return KV_OK;
 }
 

@@ -234,8 +234,11 @@ kv_status objectives(const kv_config* cfg_dev, uint32_t n_cfg, uint32_t n_groups
                      const uint64_t* counts, const double* store_cg, const kv_cost_model& m,
                      double gb, double tpg, double span, double n_req, uint64_t n_w,
                      double* obj, hipStream_t s);
+// nan_seen (device, zero between calls) and result (host memory the device
+// writes {flagged rows, NaN seen} to) serve one call at a time; result NULL:
+// neither is used.
 kv_status pareto(const double* obj, const uint32_t* segment, uint32_t n, const double* bounds,
-                 uint8_t* flag, uint32_t* counters_dev, hipStream_t s);
+                 uint8_t* flag, uint32_t* nan_seen, uint32_t* result, hipStream_t s);
 
 // TTL curves (k_ttl.hip): validated arguments; ttl_dev holds the n_ttl
 // thresholds on the device.
