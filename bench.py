@@ -69,7 +69,7 @@ def parse():
                     help="of the measurements after the timed steps, only the TTL curves")
     ap.add_argument("--exclusive-extra-only", action="store_true",
                     help="of the measurements after the timed steps, only the exclusive "
-                         "hierarchies replayed access by access")
+                         "hierarchies that are no split stack")
     ap.add_argument("--copy-calibration", type=int, default=0, metavar="BYTES",
                     help="first run one plain device-to-device copy of BYTES (a reference "
                          "for hardware byte counters)")

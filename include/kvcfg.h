@@ -61,11 +61,10 @@ enum {
    * insertion; LFU: count 1, touched now (one touch sequence per
    * hierarchy) - and the tier passes its own victims down, each entering
    * the next tier the same way, before it admits the block.  LRU over blocks
-   * of one weight is evaluated as a split stack; FIFO, LFU and LRU over
-   * mixed weights replay the trace once per configuration, one access after
-   * another (about a microsecond per access and configuration: meant for
-   * traces of up to some millions of accesses).  Not with LEAF, prefix
-   * reuse or a disk TTL tier. */
+   * of one weight is evaluated as a split stack; under FIFO, LFU, and LRU over
+   * mixed weights, the top tier is replayed once per distinct capacity (LRU:
+   * not at all) and each configuration walks its queue of demotions.  Not
+   * with LEAF, prefix reuse or a disk TTL tier. */
   KV_MODE_EXCLUSIVE_DEMOTE = 1,
   /* The inclusive hierarchy with prefix reuse, as in a radix-tree KV cache
    * (blocks are prefix-chained, Section 3.2): contents evolve exactly as in
@@ -265,8 +264,7 @@ kv_status kv_trace_info(const kv_trace* t, kv_trace_stats* out);
  * than 1,024 distinct TTLs per group in one call, for LEAF outside the
  * inclusive shared mode, on a trace whose requests are not prefix chains,
  * of more than 2^28 accesses or of total weight 2^31 granules or more, or
- * with a nonzero capacity below the heaviest request, for the exclusive
- * mode with FIFO/LFU or with blocks of different weights, and for the
+ * with a nonzero capacity below the heaviest request, and for the
  * prefix-reuse mode with FIFO/LFU or partitioned capacities; KV_ERR_NOMEM when not even
  * one replay job's state fits; KV_ERR_DEVICE when an earlier call's replay
  * failure (see kv_trace_info) has already arrived.  n_cfg == 0 is a no-op. */

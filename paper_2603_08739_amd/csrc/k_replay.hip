@@ -47,6 +47,7 @@ struct JobDev {
   uint64_t word0;       // first bitmap word index (begin / 64)
   uint32_t kind;        // kJobFifoChunk, kJobFifoSerial, kJobLfu
   uint32_t chunk;       // chunk length (multiple of 64)
+  uint64_t emit_off;    // u32 words into the emission pool (emitting launches)
 };
 
 enum : uint32_t { kJobFifoChunk = 0, kJobFifoSerial = 1, kJobLfu = 2 };
@@ -66,6 +67,14 @@ struct JobArgs {
   uint32_t job_lo, job_hi;  // the jobs of this launch (a wave); others return at once
   uint32_t fail_job;    // test hook: this job reports a failed state check (kNone: none)
   uint32_t* err;        // {code, job}: code 1 = an LFU job failed its state check
+  uint32_t err_base;    // added to the job's index in the error record
+  // Emitting launches (the top tiers of exclusive hierarchies) also write one
+  // word per access of the job, at emit + emit_off + (position - begin):
+  // FIFO, at a miss: the weight inserted before the block's insertion that
+  // this miss supersedes (all-ones: its first).  LFU: at the last access of
+  // a stay in the cache, how many evictions came before the stay's own (all-
+  // ones: not evicted, or not a stay's last access).
+  uint32_t* emit;
 };
 
 constexpr int kRNT = 1024;                 // threads of a replay workgroup
@@ -120,6 +129,10 @@ __global__ __launch_bounds__(256) void k_replay_init(const JobDev* __restrict__ 
     for (uint32_t f = blockIdx.x * blockDim.x + threadIdx.x; f < a.n_class;
          f += gridDim.x * blockDim.x)
       head[f] = (uint32_t)j.begin;
+    if (a.emit)
+      for (uint64_t p = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; p < j.end - j.begin;
+           p += (uint64_t)gridDim.x * blockDim.x)
+        a.emit[j.emit_off + p] = kNone;
   }
 }
 
@@ -355,6 +368,7 @@ __device__ __forceinline__ void issue_inputs(const JobDev& j, const JobArgs& a, 
 // ---------------------------------------------------------------------------
 constexpr uint32_t kNoIns32 = 0xFFFFFFFFu;
 
+template <bool kEmit>
 __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
                                              uint32_t* __restrict__ S,
                                              uint64_t* __restrict__ bits, GroupCounters& gc,
@@ -432,6 +446,7 @@ __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
       hit[e] = v[e] && !miss[e];
       if (v[e] && miss[e]) {
         S[A.b[e]] = wi[e];
+        if constexpr (kEmit) a.emit[j.emit_off + (c0 + l0 + e - j.begin)] = sa[e];
         if (g1) {
           ++ci;
           cw += ww[e];
@@ -505,6 +520,7 @@ __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
 
 // FIFO for capacities below 64 blocks: lanes of wave 0 gather a batch of 64
 // accesses, one lane resolves them in trace order.
+template <bool kEmit>
 __device__ __forceinline__ void fifo_serial(const JobDev& j, const JobArgs& a,
                                             uint32_t* __restrict__ S, uint64_t* __restrict__ bits,
                                             GroupCounters& gc) {
@@ -547,6 +563,7 @@ __device__ __forceinline__ void fifo_serial(const JobDev& j, const JobArgs& a,
           word |= 1ull << l;
           snew[l] = s;
         } else {
+          if constexpr (kEmit) a.emit[j.emit_off + (p - j.begin)] = s;
           snew[l] = wcur;
           S[sb[l]] = wcur;
           wcur += sw[l];
@@ -607,6 +624,7 @@ struct LfuLds {
   uint32_t nc, h;             // candidate scan: entries found, next position
   uint64_t vw;                // candidate scan: untouched weight found
   int ok;
+  uint32_t evn;               // evictions so far (emitting launches, after a serial walk)
   // per access of the chunk (local position).  Members of one union serve
   // the fixed point and the apply step respectively, never both at once.
   union {
@@ -767,12 +785,13 @@ __device__ __forceinline__ void lfu_serial_stage(const JobDev& j, const JobArgs&
 // equal values to one address); only the victim search spreads candidate
 // positions over the lanes.  Returns false if the state is found
 // inconsistent.
+template <bool kEmit>
 __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& a,
                                                 uint32_t* __restrict__ cnt, uint32_t* head,
                                                 uint32_t n_class, const Classes& cl, LfuLds& S,
                                                 GroupCounters& gc, uint64_t* __restrict__ bits,
                                                 uint32_t p0, uint32_t p1, uint64_t& used_io,
-                                                uint32_t& head1_io) {
+                                                uint32_t& head1_io, uint32_t& evn) {
   const uint32_t o = j.order;
   const uint32_t b0 = (uint32_t)j.begin;
   const uint32_t lane = lane_id();
@@ -859,6 +878,7 @@ __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& 
           else if (fmin < kHeadLds) S.shead[fmin] = q + 1;
           else if (fmin < kTopClass) head[fmin] = q + 1;
           cnt[q - b0] = 0;
+          if constexpr (kEmit) a.emit[j.emit_off + (q - b0)] = evn++;
           // the access that links to q reads the eviction
           if (q >= p0) S.scnt[q - p0] = 0;
           else if (nq != kNone && nq < p1) S.s0[nq - p0] = 0;
@@ -971,13 +991,13 @@ struct LfuAhead {
   uint4 key[IT / 4];
 };
 
-template <int NT, bool G1>
+template <int NT, bool G1, bool kEmit>
 __device__ __forceinline__ bool lfu_fast(const JobDev& j, const JobArgs& a,
                                          uint32_t* __restrict__ cnt, const Classes& cl,
                                          GroupCounters& gc, LfuLds& S,
                                          uint64_t* __restrict__ bits, uint32_t c0, uint32_t c1,
                                          uint32_t g0, BlockAny& block_any, bool have_pref,
-                                         uint64_t& used_io, uint32_t& head1_io,
+                                         uint64_t& used_io, uint32_t& head1_io, uint32_t& evn,
                                          LfuAhead<kLChunk / NT>& ahead) {
   constexpr bool g1 = G1;
   constexpr int IT = kLChunk / NT;               // accesses per thread
@@ -1487,6 +1507,32 @@ __device__ __forceinline__ bool lfu_fast(const JobDev& j, const JobArgs& a,
     lm[e] = (uint32_t)(int32_t)lmB[loc];
     oc[e] = ocB[loc];
   }
+  if constexpr (kEmit) {
+    // the chunk's evictions in queue order: the old entries taken, then the
+    // chunk's own insertions taken (none without a demand)
+    if (ev0 > 0) {
+      constexpr int CT = (int)kCand / NT;
+      uint32_t xo = 0, xn = 0, po, pn, to, tn;
+#pragma unroll
+      for (int e = 0; e < CT; ++e) {
+        const uint32_t k = tid * CT + e;
+        xo += k < nc0 && S.ccons[k] ? 1u : 0u;
+      }
+#pragma unroll
+      for (int e = 0; e < IT; ++e) xn += v[e] && miss[e] && mc[e] ? 1u : 0u;
+      block_excl_scan2_u32<NT, false>(xo, xn, S.red[rg++ & 1], po, pn, to, tn);
+      uint32_t* out = a.emit + j.emit_off;
+#pragma unroll
+      for (int e = 0; e < CT; ++e) {
+        const uint32_t k = tid * CT + e;
+        if (k < nc0 && S.ccons[k]) out[S.cq[k] - jb] = evn + po++;
+      }
+#pragma unroll
+      for (int e = 0; e < IT; ++e)
+        if (v[e] && miss[e] && mc[e]) out[p0 + e - jb] = evn + to + pn++;
+      evn += to + tn;
+    }
+  }
   uint32_t mocc[IT], mcm[IT], rf0[IT];
 #pragma unroll
   for (int e = 0; e < IT; ++e) {
@@ -1624,7 +1670,7 @@ __device__ __forceinline__ bool lfu_fast(const JobDev& j, const JobArgs& a,
   return true;
 }
 
-template <int NT, bool G1>
+template <int NT, bool G1, bool kEmit>
 __device__ __forceinline__ void lfu_chunked(const JobDev& j, const JobArgs& a,
                                             uint32_t* __restrict__ cnt, uint32_t* __restrict__ cls,
                                             uint64_t* __restrict__ bits, GroupCounters& gc,
@@ -1648,11 +1694,12 @@ __device__ __forceinline__ void lfu_chunked(const JobDev& j, const JobArgs& a,
   uint64_t ppos = ~0ull;  // the chunk whose links and counts are prefetched in LDS
   uint64_t used = 0;                    // cached weight
   uint32_t head1 = (uint32_t)j.begin;   // no live count-1 member before head1
+  uint32_t evn = 0;                     // evictions so far (emitting launches)
   LfuAhead<kLChunk / NT> ahead;
   while (pos < j.end) {
     const uint32_t l = (uint32_t)min<uint64_t>(len, j.end - pos);
-    if (lfu_fast<NT, G1>(j, a, cnt, cl, gc, S, bits, (uint32_t)pos, (uint32_t)(pos + l), g0,
-                         block_any, ppos == pos, used, head1, ahead)) {
+    if (lfu_fast<NT, G1, kEmit>(j, a, cnt, cl, gc, S, bits, (uint32_t)pos, (uint32_t)(pos + l),
+                                g0, block_any, ppos == pos, used, head1, evn, ahead)) {
       ppos = (l == kLChunk) ? pos + l : ~0ull;
       pos += l;
       len = min<uint32_t>(len * 2, j.chunk);
@@ -1665,9 +1712,11 @@ __device__ __forceinline__ void lfu_chunked(const JobDev& j, const JobArgs& a,
       lfu_serial_stage<NT>(j, a, cnt, head, a.n_class, S, (uint32_t)pos, (uint32_t)(pos + l));
       __syncthreads();
       if (wave_id() == 0) {
-        const bool ok = lfu_serial_wave(j, a, cnt, head, a.n_class, cl, S, gc, bits,
-                                        (uint32_t)pos, (uint32_t)(pos + l), used, head1);
+        const bool ok = lfu_serial_wave<kEmit>(j, a, cnt, head, a.n_class, cl, S, gc, bits,
+                                               (uint32_t)pos, (uint32_t)(pos + l), used, head1,
+                                               evn);
         if (lane_id() == 0) {
+          if constexpr (kEmit) S.evn = evn;
           S.ok = ok ? 1 : 0;
           S.used = used;
           S.head1 = head1;
@@ -1676,6 +1725,7 @@ __device__ __forceinline__ void lfu_chunked(const JobDev& j, const JobArgs& a,
       __syncthreads();
       used = S.used;
       head1 = S.head1;
+      if constexpr (kEmit) evn = S.evn;
       if (!S.ok) break;
       pos += l;
       ppos = ~0ull;
@@ -1707,6 +1757,7 @@ __device__ __forceinline__ JobArgs job_args(const JobArgs& a_in, JobDev& j) {
 }
 
 // FIFO jobs (LFU jobs are left to k_replay_lfu).
+template <bool kEmit>
 __global__ __launch_bounds__(kRNT) void k_replay(const JobDev* __restrict__ jobs, JobArgs a_in,
                                                  uint64_t* __restrict__ state,
                                                  uint64_t* __restrict__ bits,
@@ -1725,17 +1776,17 @@ __global__ __launch_bounds__(kRNT) void k_replay(const JobDev* __restrict__ jobs
   const uint32_t g0 = j.group == KV_MAX_GROUPS ? 0u : j.group;
   unsigned long long* cnt = jcnt + (uint64_t)blockIdx.x * a.n_groups * 4;
   if (j.kind == kJobFifoChunk)
-    fifo_chunked(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), bits + j.bits_off, gc,
-                 lds, g1, g0);
+    fifo_chunked<kEmit>(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), bits + j.bits_off, gc,
+                        lds, g1, g0);
   else
-    fifo_serial(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), bits + j.bits_off, gc);
+    fifo_serial<kEmit>(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), bits + j.bits_off, gc);
   __syncthreads();
   write_counters(gc, a.n_groups, cnt);
 }
 
 // LFU jobs, NT threads per job; G1: the jobs whose accesses all belong to
 // one group (the others are left to the G1 = false instance).
-template <int NT, bool G1>
+template <int NT, bool G1, bool kEmit>
 __global__ __launch_bounds__(NT) void k_replay_lfu(const JobDev* __restrict__ jobs, JobArgs a_in,
                                                    uint64_t* __restrict__ state,
                                                    uint32_t* __restrict__ cls,
@@ -1753,13 +1804,13 @@ __global__ __launch_bounds__(NT) void k_replay_lfu(const JobDev* __restrict__ jo
   __syncthreads();
   const uint32_t g0 = j.group == KV_MAX_GROUPS ? 0u : j.group;
   unsigned long long* cnt = jcnt + (uint64_t)blockIdx.x * a.n_groups * 4;
-  lfu_chunked<NT, G1>(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), cls,
-                      bits + j.bits_off, gc, lds, g0);
+  lfu_chunked<NT, G1, kEmit>(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), cls,
+                             bits + j.bits_off, gc, lds, g0);
   const bool ok = lds.ok != 0 && blockIdx.x != a.fail_job;
   __syncthreads();
   write_counters(gc, a.n_groups, cnt);
   // a failed state check is recorded for the host (the first failing job wins)
-  if (tid == 0 && !ok && atomicCAS(&a.err[0], 0u, 1u) == 0u) atomicExch(&a.err[1], blockIdx.x);
+  if (tid == 0 && !ok && atomicCAS(&a.err[0], 0u, 1u) == 0u) atomicExch(&a.err[1], a.err_base + blockIdx.x);
 }
 
 // Per order: re-access bits (key != 0), weight bit-planes, group masks.
@@ -2139,6 +2190,117 @@ static uint32_t replay_test_fail_job() {
   return e ? (uint32_t)std::strtoul(e, nullptr, 10) : kNone;
 }
 
+// How a job is replayed, from its policy and capacity.
+static void job_shape(JobDev& j, uint32_t w_max) {
+  if (j.policy == KV_POLICY_FIFO) {
+    const uint64_t lc = std::min<uint64_t>(kRChunk, (j.cap / std::max<uint32_t>(w_max, 1)) & ~63ull);
+    j.kind = lc >= 64 ? kJobFifoChunk : kJobFifoSerial;
+    j.chunk = (uint32_t)std::max<uint64_t>(lc, 64);
+  } else {
+    j.kind = kJobLfu;
+    j.chunk = kLChunk;
+  }
+}
+
+// The orders' arrays, as every replay launch reads them.
+static JobArgs order_args(const Trace& t) {
+  const bool have_part = t.part.built;
+  JobArgs ja{};
+  ja.bid[0] = t.shared.bid.as<uint32_t>();
+  ja.key[0] = t.shared.key.as<uint32_t>();
+  ja.nxt[0] = t.shared.nxt.as<uint32_t>();
+  ja.key[1] = have_part ? t.part.key.as<uint32_t>() : ja.key[0];
+  ja.nxt[1] = have_part ? t.part.nxt.as<uint32_t>() : ja.nxt[0];
+  ja.w8[0] = t.shared.w.as<uint8_t>();
+  ja.g8[0] = t.shared.g.as<uint8_t>();
+  ja.bid[1] = have_part ? t.part.bid.as<uint32_t>() : ja.bid[0];
+  ja.w8[1] = have_part ? t.part.w.as<uint8_t>() : ja.w8[0];
+  ja.g8[1] = have_part ? t.part.g.as<uint8_t>() : ja.g8[0];
+  ja.blk_w = t.blk_w.as<uint8_t>();
+  ja.blk_g = t.blk_g.as<uint8_t>();
+  ja.u = t.u;
+  ja.n = t.n;
+  ja.n_groups = t.n_groups;
+  ja.n_class = kLdsClass;
+  ja.err = t.err.as<uint32_t>();
+  ja.fail_job = kNone;
+  return ja;
+}
+
+EmitLayout emit_layout(const Trace& t, uint32_t policy, uint64_t n) {
+  EmitLayout l;
+  const bool lfu = policy == KV_POLICY_LFU;
+  l.state = lfu ? (n + 2) / 2 * 8 : (t.u + 1) / 2 * 8;
+  l.classes = lfu ? kLdsClass * 4 : 0;
+  return l;
+}
+
+kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab, uint8_t* tables,
+                      std::vector<uint8_t>& stage, unsigned long long* jcnt, uint32_t err_base,
+                      hipStream_t s) {
+  const uint32_t nj = (uint32_t)jobs.size();
+  const size_t at = stage.size();
+  stage.resize(at + nj * sizeof(JobDev));
+  bool fifo = false, one = false, many = false;
+  for (uint32_t i = 0; i < nj; ++i) {
+    const EmitJob& e = jobs[i];
+    JobDev j{};
+    j.order = e.job.order;
+    j.group = e.job.group;
+    j.policy = e.job.policy;
+    j.cap = e.job.cap;
+    j.begin = e.job.begin;
+    j.end = e.job.end;
+    j.word0 = e.job.begin >> 6;
+    job_shape(j, t.st.w_max);
+    j.state_off = e.state / 8;
+    j.class_off = e.classes / 4;
+    j.bits_off = e.bits / 8;
+    j.emit_off = e.emit / 4;
+    std::memcpy(stage.data() + at + i * sizeof(JobDev), &j, sizeof(JobDev));
+    if (j.kind != kJobLfu) fifo = true;
+    else if (lfu_one_group(j, t.n_groups)) one = true;
+    else many = true;
+  }
+  KV_HIP(hipMemcpyAsync(tables, stage.data() + at, nj * sizeof(JobDev), hipMemcpyHostToDevice, s));
+  const JobDev* jd = reinterpret_cast<const JobDev*>(tables);
+  JobArgs a = order_args(t);
+  a.job_lo = 0;
+  a.job_hi = nj;
+  a.err_base = err_base;
+  a.emit = reinterpret_cast<uint32_t*>(slab);
+  uint64_t* state = reinterpret_cast<uint64_t*>(slab);
+  uint32_t* cls = reinterpret_cast<uint32_t*>(slab);
+  hipLaunchKernelGGL(k_replay_init, dim3(64, nj), dim3(256), 0, s, jd, state, cls, a);
+  KV_HIP(hipGetLastError());
+  // the kernels of different policies run beside each other
+  AuxStream* aux = nullptr;
+  if (kv_status st = aux_stream(&aux)) return st;
+  std::unique_lock<std::mutex> lk(aux->mu);
+  KV_HIP(hipEventRecord(aux->fork, s));
+  const bool any[kAux] = {one, many, fifo};
+  for (int k = 0; k < kAux; ++k) {
+    if (!any[k]) continue;
+    hipStream_t sk = aux->s[k];
+    KV_HIP(hipStreamWaitEvent(sk, aux->fork, 0));
+    if (k == 0)
+      hipLaunchKernelGGL((k_replay_lfu<kLfuNT, true, true>), dim3(nj), dim3(kLfuNT), 0, sk, jd, a,
+                         state, cls, state, jcnt);
+    else if (k == 1)
+      hipLaunchKernelGGL((k_replay_lfu<kLfuNT, false, true>), dim3(nj), dim3(kLfuNT), 0, sk, jd, a,
+                         state, cls, state, jcnt);
+    else
+      hipLaunchKernelGGL(k_replay<true>, dim3(nj), dim3(kRNT), 0, sk, jd, a, state, state, jcnt);
+    KV_HIP(hipGetLastError());
+    KV_HIP(hipEventRecord(aux->join[k], sk));
+  }
+  for (int k = 0; k < kAux; ++k)
+    if (any[k]) KV_HIP(hipStreamWaitEvent(s, aux->join[k], 0));
+  return KV_OK;
+}
+
+uint64_t emit_table_bytes() { return sizeof(JobDev); }
+
 kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_config* cfg_host,
                      const kv_config* cfg_dev, uint32_t n_cfg, uint64_t* counts,
                      hipStream_t s, const std::function<kv_status()>& meanwhile) {
@@ -2164,14 +2326,7 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
     j.begin = r.begin;
     j.end = r.end;
     j.word0 = r.begin >> 6;
-    if (r.policy == KV_POLICY_FIFO) {
-      const uint64_t lc = std::min<uint64_t>(kRChunk, (r.cap / std::max<uint32_t>(t.st.w_max, 1)) & ~63ull);
-      j.kind = lc >= 64 ? kJobFifoChunk : kJobFifoSerial;
-      j.chunk = (uint32_t)std::max<uint64_t>(lc, 64);
-    } else {
-      j.kind = kJobLfu;
-      j.chunk = kLChunk;
-    }
+    job_shape(j, t.st.w_max);
     if (!r.closed && r.end > r.begin) {
       // FIFO: one u32 per block; LFU: one count per position and a spare slot
       jw[i] = (r.policy == KV_POLICY_FIFO) ? (t.u + 1) / 2 : (r.end - r.begin + 2) / 2;
@@ -2241,7 +2396,7 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
     for (uint32_t g = 0; g < ng; ++g) {
       const uint32_t pol = C.partitioned ? C.policy[g] : C.policy[0];
       if (pol == KV_POLICY_LRU || pol == KV_POLICY_LEAF) continue;
-      if (C.mode == KV_MODE_EXCLUSIVE_DEMOTE) continue;  // replayed access by access
+      if (C.mode == KV_MODE_EXCLUSIVE_DEMOTE) continue;  // walked (k_excl.hip)
       const uint32_t ord = part_order ? 1u : 0u;
       const uint32_t grp = part_order ? g : (uint32_t)KV_MAX_GROUPS;
       // a shared cache reports every group; a partitioned one only its own
@@ -2341,24 +2496,7 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
   if (!recs.empty())
     KV_HIP(hipMemcpyAsync(brec.p, t.rec_stage.data(), t.rec_stage.size(), hipMemcpyHostToDevice,
                           s));
-  JobArgs ja{};
-  ja.bid[0] = t.shared.bid.as<uint32_t>();
-  ja.key[0] = t.shared.key.as<uint32_t>();
-  ja.nxt[0] = t.shared.nxt.as<uint32_t>();
-  ja.key[1] = have_part ? t.part.key.as<uint32_t>() : ja.key[0];
-  ja.nxt[1] = have_part ? t.part.nxt.as<uint32_t>() : ja.nxt[0];
-  ja.w8[0] = t.shared.w.as<uint8_t>();
-  ja.g8[0] = t.shared.g.as<uint8_t>();
-  ja.bid[1] = have_part ? t.part.bid.as<uint32_t>() : ja.bid[0];
-  ja.w8[1] = have_part ? t.part.w.as<uint8_t>() : ja.w8[0];
-  ja.g8[1] = have_part ? t.part.g.as<uint8_t>() : ja.g8[0];
-  ja.blk_w = t.blk_w.as<uint8_t>();
-  ja.blk_g = t.blk_g.as<uint8_t>();
-  ja.u = t.u;
-  ja.n = t.n;
-  ja.n_groups = G;
-  ja.n_class = n_class;
-  ja.err = t.err.as<uint32_t>();
+  JobArgs ja = order_args(t);
   ja.fail_job = replay_test_fail_job();
   const uint32_t nj = (uint32_t)jd.size();
   auto wave_args = [&](uint32_t w) {
@@ -2470,15 +2608,15 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
   auto launch = [&](int k, hipStream_t sk, const JobArgs& x) -> kv_status {
     tm.emplace(k == 2 ? kStReplayFifo : kStReplay, sk);
     if (k == 0)
-      hipLaunchKernelGGL((k_replay_lfu<kLfuNT, true>), dim3(nj), dim3(kLfuNT), 0, sk,
+      hipLaunchKernelGGL((k_replay_lfu<kLfuNT, true, false>), dim3(nj), dim3(kLfuNT), 0, sk,
                          bj.as<JobDev>(), x, bstate.as<uint64_t>(), bcls.as<uint32_t>(),
                          bbits.as<uint64_t>(), bjc.as<unsigned long long>());
     else if (k == 1)
-      hipLaunchKernelGGL((k_replay_lfu<kLfuNT, false>), dim3(nj), dim3(kLfuNT), 0, sk,
+      hipLaunchKernelGGL((k_replay_lfu<kLfuNT, false, false>), dim3(nj), dim3(kLfuNT), 0, sk,
                          bj.as<JobDev>(), x, bstate.as<uint64_t>(), bcls.as<uint32_t>(),
                          bbits.as<uint64_t>(), bjc.as<unsigned long long>());
     else
-      hipLaunchKernelGGL(k_replay, dim3(nj), dim3(kRNT), 0, sk, bj.as<JobDev>(), x,
+      hipLaunchKernelGGL(k_replay<false>, dim3(nj), dim3(kRNT), 0, sk, bj.as<JobDev>(), x,
                          bstate.as<uint64_t>(), bbits.as<uint64_t>(),
                          bjc.as<unsigned long long>());
     KV_HIP(hipGetLastError());

@@ -681,7 +681,7 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
   bool need_shared = false, need_part = false, need_prefix = false, need_joint = false;
   const uint64_t w0 = t->st.w_max;
   const bool mixed = t->st.w_min != t->st.w_max;
-  bool need_excl = false;
+  bool need_excl = false, need_excl_part = false;
   std::map<std::tuple<uint32_t, uint32_t, uint32_t, uint64_t>, uint32_t> job_index;
   std::vector<ReplayJob> jobs;
   for (uint32_t c = 0; c < n_cfg; ++c) {
@@ -690,8 +690,9 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
     const uint32_t ng = C.partitioned ? G : 1;
     for (uint32_t g = 0; g < ng; ++g) {
       const uint32_t pol = group_policy(C, g);
-      if (excl_replayed(C, g, mixed)) {  // replayed access by access
+      if (excl_replayed(C, g, mixed)) {  // walked by itself
         need_excl = true;
+        need_excl_part |= part_order;
         continue;
       }
       if (pol == KV_POLICY_LEAF) {
@@ -736,7 +737,7 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
       }
     }
   }
-  if (need_part || (!jobs.empty() && G > 1)) {
+  if (need_part || need_excl_part || (!jobs.empty() && G > 1)) {
     if ((st = canon_partition(*t, s)) != KV_OK) return st;
   }
   for (auto& j : jobs) {
@@ -793,6 +794,7 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
                         counts, store_cg, s);
     return KV_OK;
   };
+  t->err_jobs.clear();
   // ---- FIFO / LFU: replay jobs, with the LRU work running meanwhile
   if (!jobs.empty()) {
     if ((st = replay_run(*t, jobs, cfg, cfg_dev, n_cfg, counts, s, lru)) != KV_OK) return st;
@@ -800,7 +802,7 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
     return st;
   }
   // ---- exclusive hierarchies without a split stack
-  if (need_excl && (st = excl_run(*t, cfg, cfg_dev, n_cfg, counts, s)) != KV_OK) return st;
+  if (need_excl && (st = excl_run(*t, cfg, n_cfg, bgs.as<GroupStats>(), counts, s)) != KV_OK) return st;
   // ---- objectives
   if (obj) {
     st = objectives(cfg_dev, n_cfg, G, counts, store_cg, *model, (double)t->gb, (double)t->tpg,

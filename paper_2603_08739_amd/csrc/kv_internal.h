@@ -144,7 +144,7 @@ struct Trace {
   std::vector<uint8_t> job_stage, rec_stage, src_stage;
   std::vector<double> ttl_stage;
   std::vector<unsigned long long> jc_stage;
-  std::vector<uint8_t> excl_stage;
+  std::vector<uint8_t> excl_stage, emit_stage;
 };
 
 constexpr uint64_t kTraceMagic = 0x6b7663666774726bull;  // "kvcfgtrk"
@@ -274,14 +274,37 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
                      const kv_config* cfg_dev, uint32_t n_cfg, uint64_t* counts,
                      hipStream_t s, const std::function<kv_status()>& meanwhile);
 
-// exclusive hierarchies replayed access by access (k_excl.hip)
+// The top tiers of exclusive hierarchies: jobs replayed with an emission, one
+// u32 per access of the job (what it holds: JobArgs in k_replay.hip).  The
+// byte offsets lie in one buffer, each a multiple of 256.
+struct EmitJob {
+  ReplayJob job;
+  uint64_t state, classes;   // replay state, sizes from emit_layout
+  uint64_t bits;             // hit words of positions begin / 64 .. (end - 1) / 64
+  uint64_t emit;             // u32[end - begin]
+};
+struct EmitLayout {
+  uint64_t state, classes;   // bytes
+};
+EmitLayout emit_layout(const Trace& t, uint32_t policy, uint64_t n);
+uint64_t emit_table_bytes();  // device table bytes per job
+// jcnt: [jobs][n_groups][4] insertions, their weight, evictions, their weight
+// (written); tables: device memory for the job table, staged at the end of
+// `stage`, which must not move while the copy is in flight; a job that fails
+// its state check is recorded as err_base + its index.
+kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab, uint8_t* tables,
+                      std::vector<uint8_t>& stage, unsigned long long* jcnt, uint32_t err_base,
+                      hipStream_t s);
+
+// exclusive hierarchies without a split stack (k_excl.hip)
 // Whether hierarchy g of C (group g when partitioned, 0 otherwise) is
-// replayed there: the exclusive mode under FIFO or LFU, or under LRU when
+// evaluated there: the exclusive mode under FIFO or LFU, or under LRU when
 // the trace's blocks have mixed weights (otherwise a split stack serves it).
 bool excl_replayed(const kv_config& C, uint32_t g, bool mixed);
-// Writes the records of every replayed hierarchy of the batch (the records
-// of a shared hierarchy: every group).
-kv_status excl_run(Trace& t, const kv_config* cfg_host, const kv_config* cfg_dev,
-                   uint32_t n_cfg, uint64_t* counts, hipStream_t s);
+// Writes the records of every such hierarchy of the batch (the records of a
+// shared hierarchy: every group).  With partitioned configurations over
+// several groups t.part must be built.
+kv_status excl_run(Trace& t, const kv_config* cfg_host, uint32_t n_cfg, const GroupStats* gs_dev,
+                   uint64_t* counts, hipStream_t s);
 
 }  // namespace kv
