@@ -12,8 +12,9 @@
 // With p = prev(i) and key_j = prev(j) + 1 (0 for a first access):
 //   D_i = w_i + sum_{p < j < i} w_j [key_j <= p]
 // (a block touched in (p, i) is counted at its first touch there, the one
-// whose own previous access lies before p).  Positions are cut into 8192-wide
-// blocks; with P = block(p), I = block(i):
+// whose own previous access lies before p).  Positions are cut into blocks of
+// B (1,024 to 8,192 by the length of the trace); with P = block(p),
+// I = block(i):
 //   P == I:  D_i = w_i + A(i) - Wloc(p)
 //   P <  I:  D_i = w_i + A(i) + E(p) + RQ[I-1][P]
 // where, inside one block,
@@ -22,8 +23,13 @@
 //   E(p)    = Cnt_P(p) - Wloc(p) + C(p)
 //   Cnt_P(p)= sum_{j in block P} w_j [key_j <= p]
 //   C(p)    = sum_{q in block P, q < p} w_q [P < block(next(q)) < block(next(p))]
-// and across blocks RQ[X][Y] = sum_{X'=Y+1..X} Q[X'][Y] with
-//   Q[X][Y] = sum_{j in block X} w_j [key_j <= Y * 8192]
+// A key at most p is either below the block or the link of a q < p of the
+// block, so with S(p) = sum_{q in block P, q < p} w_q [block(next(q)) = P]:
+//   Cnt_P(p) = (weight of block P - S(end of P)) + S(p),  and
+//   C(p) + S(p) = N(p) = sum_{q in block P, q < p} w_q [block(next(q)) < block(next(p))]:
+//   E(p)    = (weight of block P - S(end of P)) - Wloc(p) + N(p).
+// Across blocks RQ[X][Y] = sum_{X'=Y+1..X} Q[X'][Y] with
+//   Q[X][Y] = sum_{j in block X} w_j [key_j <= Y * B]
 // stored as a lower triangle.  The two in-block dominance counts come from
 // an LDS merge sort that accumulates, for every element of a right-hand run,
 // the weight of smaller keys in the left-hand run.
@@ -35,6 +41,7 @@
 // return, so hits(C) is one lookup.
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
 
 #include "kv_device.h"
 #include "kv_internal.h"
@@ -42,9 +49,7 @@
 namespace kv {
 namespace {
 
-constexpr int kLocNT = 1024;
-constexpr int kLocItems = 8;
-static_assert(kLocNT * kLocItems == (int)kSdB, "block tile mismatch");
+constexpr int kLocItems = 8;            // positions per thread of the in-block sorts
 constexpr uint32_t kSentinel = 0xFFFFFFFFu;
 constexpr uint32_t kRowChunk = 16384;   // LDS histogram bins per row chunk
 constexpr int kRowNT = 1024;            // threads per row of the block matrix
@@ -55,11 +60,12 @@ constexpr uint32_t kThrLds = 6144;      // thresholds kept in LDS for binning
 __host__ __device__ __forceinline__ uint64_t tri_off(uint64_t x) { return x * (x - 1) / 2; }
 
 // ---------------------------------------------------------------------------
-// Q rows: Q[X][Y] for Y < X, inclusive prefix over ceil(key / 8192).
+// Q rows: Q[X][Y] for Y < X, inclusive prefix over ceil(key / B).
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restrict__ key,
                                                     const uint8_t* __restrict__ w8, uint64_t n,
-                                                    uint32_t row_chunk, uint32_t* __restrict__ Q) {
+                                                    uint32_t logb, uint32_t row_chunk,
+                                                    uint32_t* __restrict__ Q) {
   // bin j lives at hp(j), one padding word after every 64: the scan below
   // gives each thread a run of up to kRowChunk / kRowNT bins, which would
   // otherwise put the lanes of a wavefront on a few banks
@@ -68,8 +74,8 @@ __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restric
   const auto hp = [](uint32_t j) { return j + (j >> 6); };
   const uint32_t X = blockIdx.x;
   if (X == 0) return;
-  const uint64_t base = (uint64_t)X * kSdB;
-  const uint32_t nb = (uint32_t)min<uint64_t>(kSdB, n - base);
+  const uint64_t base = (uint64_t)X << logb;
+  const uint32_t nb = (uint32_t)min<uint64_t>(1ull << logb, n - base);
   const uint64_t row = tri_off(X);
   for (uint32_t c0 = 0; c0 < X; c0 += row_chunk) {
     const uint32_t width = min(row_chunk, X - c0);
@@ -77,7 +83,7 @@ __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restric
     __syncthreads();
     uint32_t carry = 0;
     for (uint32_t j = threadIdx.x; j < nb; j += kRowNT) {
-      const uint32_t c = (key[base + j] + (kSdB - 1)) >> kSdLogB;
+      const uint32_t c = (key[base + j] + ((1u << logb) - 1u)) >> logb;
       const uint32_t w = w8[base + j];
       if (c < c0) carry += w;
       else if (c < c0 + width) atomicAdd(&h[hp(c - c0)], w);
@@ -141,38 +147,38 @@ __global__ __launch_bounds__(256) void k_sd_colapply(uint32_t* __restrict__ Q, u
 // In-block dominance by LDS merge sort.
 // ---------------------------------------------------------------------------
 // Element i of a block-wide LDS array lives at pd(i): one padding word after
-// every 16, so that the 16-element runs of the threads of a wavefront (and
-// the merge positions inside them, about 8 apart) fall into different banks.
-constexpr uint32_t kSdPad = kSdB + kSdB / 16;
-__device__ __forceinline__ uint32_t pd(uint32_t i) { return i + (i >> 4); }
+// every 16, so that the 8-element runs of the threads of a wavefront (and
+// the merge positions inside them) fall into different banks.
+__host__ __device__ constexpr uint32_t pd(uint32_t i) { return i + (i >> 4); }
 
+// The sorts' LDS.  Per element its key and
+//   one weight (kUni):  tag = count of smaller keys at earlier positions << 13 | position
+//   mixed weights:      tag = position, acc = weight of smaller keys at earlier positions,
+//                       pw  = inclusive prefix weight inside the element's run
+// With one weight a run's prefix weight is the index in the run, so half the
+// words move per merge and two workgroups of 8,192 fit a compute unit.
+template <int kLogB, bool kUni>
 struct SortLds {
-  uint32_t v[kSdPad];     // sorted keys of the current runs
-  uint32_t pw[kSdPad];    // inclusive prefix weight inside each run
-  uint32_t acc[kSdPad];   // accumulated weight of smaller keys at earlier positions
-  uint16_t idx[kSdPad];   // local position of the element
+  using Tag = std::conditional_t<kUni, uint32_t, uint16_t>;
+  static constexpr uint32_t kPad = pd(1u << kLogB);
+  uint32_t v[kPad];
+  Tag tag[kPad];
+  uint32_t acc[kUni ? 1 : kPad];
+  uint32_t pw[kUni ? 1 : kPad];
 };
 
-// First index in S.v[lo, hi) (padded, sorted) with a value > x.
-__device__ __forceinline__ uint32_t upper_bound_pd(const uint32_t* a, uint32_t lo, uint32_t hi,
-                                                   uint32_t x) {
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi) >> 1;
-    if (a[pd(mid)] <= x) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
-template <int N>
+template <int N, bool kUni>
 __device__ __forceinline__ void cswap(uint32_t (&v)[N], uint32_t (&w)[N], uint32_t (&a)[N],
                                       uint32_t (&x)[N], int i, int l, bool up) {
   const bool sw = (v[i] > v[l]) == up;
   if (sw) {
     uint32_t t;
     t = v[i]; v[i] = v[l]; v[l] = t;
-    t = w[i]; w[i] = w[l]; w[l] = t;
-    t = a[i]; a[i] = a[l]; a[l] = t;
     t = x[i]; x[i] = x[l]; x[l] = t;
+    if (!kUni) {
+      t = w[i]; w[i] = w[l]; w[l] = t;
+      t = a[i]; a[i] = a[l]; a[l] = t;
+    }
   }
 }
 
@@ -184,22 +190,25 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// On return S holds the block's elements sorted by v, each with
-// acc = sum over earlier positions j of w_j [v_j < v] (exact whenever v is
-// unique in the block, i.e. for every element whose acc is used).
-__device__ void block_sort_dominance(SortLds& S, const uint32_t (&vin)[kLocItems],
+// On return S holds the block's elements sorted by v, each with its position
+// and the weight (kUni: number) of smaller keys at earlier positions - exact
+// whenever v is unique in the block, i.e. for every element that uses it.
+template <int kLogB, bool kUni>
+__device__ void block_sort_dominance(SortLds<kLogB, kUni>& S, const uint32_t (&vin)[kLocItems],
                                      const uint32_t (&win)[kLocItems]) {
+  constexpr uint32_t kB = 1u << kLogB;
   const uint32_t t = threadIdx.x;
   uint32_t v[kLocItems], w[kLocItems], a[kLocItems], x[kLocItems];
 #pragma unroll
   for (int e = 0; e < kLocItems; ++e) {
     v[e] = vin[e];
     w[e] = win[e];
-    x[e] = t * kLocItems + e;
     uint32_t s = 0;
 #pragma unroll
-    for (int f = 0; f < e; ++f) s += (vin[f] < vin[e]) ? win[f] : 0u;
+    for (int f = 0; f < e; ++f) s += (vin[f] < vin[e]) ? (kUni ? 1u : win[f]) : 0u;
     a[e] = s;
+    x[e] = t * kLocItems + e;
+    if (kUni) x[e] |= s << 13;
   }
   // bitonic network on the thread's register-resident elements
 #pragma unroll
@@ -209,22 +218,24 @@ __device__ void block_sort_dominance(SortLds& S, const uint32_t (&vin)[kLocItems
 #pragma unroll
       for (int i = 0; i < kLocItems; ++i) {
         const int l = i ^ j;
-        if (l > i) cswap<kLocItems>(v, w, a, x, i, l, (i & k) == 0);
+        if (l > i) cswap<kLocItems, kUni>(v, w, a, x, i, l, (i & k) == 0);
       }
     }
   }
   uint32_t run = 0;
 #pragma unroll
   for (int e = 0; e < kLocItems; ++e) {
-    run += w[e];
     const uint32_t s = pd(t * kLocItems + e);
     S.v[s] = v[e];
-    S.pw[s] = run;
-    S.acc[s] = a[e];
-    S.idx[s] = (uint16_t)x[e];
+    S.tag[s] = (typename SortLds<kLogB, kUni>::Tag)x[e];
+    if (!kUni) {
+      run += w[e];
+      S.pw[s] = run;
+      S.acc[s] = a[e];
+    }
   }
   uint32_t pw[kLocItems];
-  for (uint32_t s = kLocItems; s < kSdB; s <<= 1) {
+  for (uint32_t s = kLocItems; s < kB; s <<= 1) {
     // a pair of runs of s spans 2s / kLocItems threads: up to 64, one wavefront
     const bool in_wave = 2 * s <= 64u * kLocItems;
     if (in_wave) wave_sync_lds(); else __syncthreads();
@@ -238,23 +249,38 @@ __device__ void block_sort_dominance(SortLds& S, const uint32_t (&vin)[kLocItems
       if (S.v[pd(Lb + mid)] <= S.v[pd(Rb + d0 - mid - 1)]) lo = mid + 1; else hi = mid;
     }
     uint32_t ia = lo, ib = d0 - lo;
+    if constexpr (kUni) {
+      uint32_t vl = S.v[pd(Lb + min(ia, s - 1))], vr = S.v[pd(Rb + min(ib, s - 1))];
 #pragma unroll
-    for (int e = 0; e < kLocItems; ++e) {
-      const uint32_t li = pd(Lb + ia), ri = pd(Rb + ib);
-      const bool takeL = (ib >= s) || (ia < s && S.v[li] <= S.v[ri]);
-      if (takeL) {
-        v[e] = S.v[li];
-        a[e] = S.acc[li];
-        x[e] = S.idx[li];
-        pw[e] = S.pw[li] + (ib ? S.pw[pd(Rb + ib - 1)] : 0u);
-        ++ia;
-      } else {
-        const uint32_t pl = ia ? S.pw[pd(Lb + ia - 1)] : 0u;
-        v[e] = S.v[ri];
-        a[e] = S.acc[ri] + pl;
-        x[e] = S.idx[ri];
-        pw[e] = pl + S.pw[ri];
-        ++ib;
+      for (int e = 0; e < kLocItems; ++e) {
+        const bool takeL = (ib >= s) || (ia < s && vl <= vr);
+        v[e] = takeL ? vl : vr;
+        x[e] = S.tag[pd(takeL ? Lb + ia : Rb + ib)] + (takeL ? 0u : ia << 13);
+        ia += takeL ? 1u : 0u;
+        ib += takeL ? 0u : 1u;
+        const uint32_t nv = S.v[pd(takeL ? Lb + min(ia, s - 1) : Rb + min(ib, s - 1))];
+        vl = takeL ? nv : vl;
+        vr = takeL ? vr : nv;
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < kLocItems; ++e) {
+        const uint32_t li = pd(Lb + ia), ri = pd(Rb + ib);
+        const bool takeL = (ib >= s) || (ia < s && S.v[li] <= S.v[ri]);
+        if (takeL) {
+          v[e] = S.v[li];
+          a[e] = S.acc[li];
+          x[e] = S.tag[li];
+          pw[e] = S.pw[li] + (ib ? S.pw[pd(Rb + ib - 1)] : 0u);
+          ++ia;
+        } else {
+          const uint32_t pl = ia ? S.pw[pd(Lb + ia - 1)] : 0u;
+          v[e] = S.v[ri];
+          a[e] = S.acc[ri] + pl;
+          x[e] = S.tag[ri];
+          pw[e] = pl + S.pw[ri];
+          ++ib;
+        }
       }
     }
     if (in_wave) wave_sync_lds(); else __syncthreads();
@@ -262,114 +288,135 @@ __device__ void block_sort_dominance(SortLds& S, const uint32_t (&vin)[kLocItems
     for (int e = 0; e < kLocItems; ++e) {
       const uint32_t o = pd(o0 + e);
       S.v[o] = v[e];
-      S.acc[o] = a[e];
-      S.idx[o] = (uint16_t)x[e];
-      S.pw[o] = pw[e];
+      S.tag[o] = (typename SortLds<kLogB, kUni>::Tag)x[e];
+      if (!kUni) {
+        S.acc[o] = a[e];
+        S.pw[o] = pw[e];
+      }
     }
   }
   __syncthreads();
 }
 
 // Per position block: A(i) and same-block distances -> partial[i]; E(p) for
-// positions whose next access lies in a later block.
-__global__ __launch_bounds__(kLocNT, 1) void k_sd_local(const uint32_t* __restrict__ key,
-                                                        const uint32_t* __restrict__ nxt,
-                                                        const uint8_t* __restrict__ w8,
-                                                        uint64_t n, uint32_t G,
-                                                        uint32_t* __restrict__ partial,
-                                                        uint32_t* __restrict__ E) {
-  __shared__ SortLds S;
-  __shared__ uint32_t P[kSdPad];   // padded like S
-  __shared__ uint32_t sh[kLocNT / 64 + 1];
+// positions whose next access lies in a later block.  Bound by the LDS
+// traffic and latency of the two merge sorts: with one weight an element
+// moves two words per merge level instead of four, and two workgroups of
+// 8,192 share a compute unit (1.09e8 accesses, blocks of 8,192: 6.7 -> 2.7
+// ms; E(p) needs no search, see the top of the file).
+// w0: the weight of every access (kUni).
+template <int kLogB, bool kUni>
+__global__ __launch_bounds__((1 << kLogB) / kLocItems, kUni ? 8 : 1) void k_sd_local(
+    const uint32_t* __restrict__ key, const uint32_t* __restrict__ nxt,
+    const uint8_t* __restrict__ w8, uint32_t w0, uint64_t n, uint32_t G,
+    uint32_t* __restrict__ partial, uint32_t* __restrict__ E) {
+  constexpr uint32_t kB = 1u << kLogB;
+  constexpr int kNT = kB / kLocItems;
+  __shared__ SortLds<kLogB, kUni> S;
+  __shared__ uint32_t P[kUni ? 1 : pd(kB)];  // Wloc, position order (kUni: (position + 1) w0)
+  __shared__ uint32_t sh[kNT / 64 + 1];
   const uint32_t X = blockIdx.x;
-  const uint64_t base = (uint64_t)X * kSdB;
-  const uint32_t nb = (uint32_t)min<uint64_t>(kSdB, n - base);
+  const uint64_t base = (uint64_t)X << kLogB;
+  const uint32_t nb = (uint32_t)min<uint64_t>(kB, n - base);
   const uint32_t t = threadIdx.x;
-  for (uint32_t j = t; j < kSdB; j += kLocNT) {
+  uint32_t* nextw;  // the next links, staged before the sorts
+  if constexpr (kUni) nextw = S.tag;
+  else nextw = S.acc;
+  for (uint32_t j = t; j < kB; j += kNT) {
     const bool in = j < nb;
     S.v[pd(j)] = in ? key[base + j] : kSentinel;
-    S.acc[pd(j)] = in ? nxt[base + j] : kNone;
-    S.pw[pd(j)] = in ? (uint32_t)w8[base + j] : 0u;
+    nextw[pd(j)] = in ? nxt[base + j] : kNone;
+    if (!kUni) S.pw[pd(j)] = in ? (uint32_t)w8[base + j] : 0u;
   }
   __syncthreads();
   uint32_t k[kLocItems], nx[kLocItems], w[kLocItems];
+  uint32_t run = 0, same = 0;  // weight (kUni: number) of positions, and of those with next here
 #pragma unroll
   for (int e = 0; e < kLocItems; ++e) {
     const uint32_t j = pd(t * kLocItems + e);
     k[e] = S.v[j];
-    nx[e] = S.acc[j];
-    w[e] = S.pw[j];
+    nx[e] = nextw[j];
+    w[e] = kUni ? (t * kLocItems + e < nb ? 1u : 0u) : S.pw[j];
+    run += w[e];
+    same += nx[e] != kNone && (nx[e] >> kLogB) == X ? w[e] : 0u;
+  }
+  const uint32_t below = block_sum<kNT>(run - same, sh);  // weight of keys below the block
+  if constexpr (!kUni) {
+    uint32_t tot;
+    uint32_t wl = block_excl_scan<kNT>(run, sh, &tot);
+#pragma unroll
+    for (int e = 0; e < kLocItems; ++e) {
+      wl += w[e];
+      P[pd(t * kLocItems + e)] = wl;
+    }
   }
   __syncthreads();
-  // Wloc (inclusive, position order) -> P;  same-block-next prefix -> sn
-  uint32_t loc[kLocItems], sn[kLocItems];
-  uint32_t run = 0, run2 = 0;
+  // The result of sorted element s goes back to its position's slot, so that
+  // it leaves the block in position order; `mine` says which slots hold one.
+  uint32_t out[kLocItems], at[kLocItems];
+  const auto put = [&](uint32_t* __restrict__ dst, const bool (&mine)[kLocItems]) {
+    __syncthreads();
 #pragma unroll
-  for (int e = 0; e < kLocItems; ++e) {
-    run += w[e];
-    loc[e] = run;
-    sn[e] = run2;
-    const bool same = nx[e] != kNone && (nx[e] >> kSdLogB) == X;
-    run2 += same ? w[e] : 0u;
-  }
-  uint32_t tot;
-  const uint32_t pre = block_excl_scan<kLocNT>(run, sh, &tot);
-  const uint32_t pre2 = block_excl_scan<kLocNT>(run2, sh, &tot);
+    for (int e = 0; e < kLocItems; ++e) S.v[pd(at[e])] = out[e];
+    __syncthreads();
 #pragma unroll
-  for (int e = 0; e < kLocItems; ++e) {
-    P[pd(t * kLocItems + e)] = loc[e] + pre;
-    sn[e] += pre2;
-  }
+    for (int e = 0; e < kLocItems; ++e) out[e] = S.v[pd(t * kLocItems + e)];
+    const uint64_t p = base + t * kLocItems;
+    if (mine[0] && mine[1] && mine[2] && mine[3])
+      *reinterpret_cast<uint4*>(dst + p) = make_uint4(out[0], out[1], out[2], out[3]);
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (mine[e]) dst[p + e] = out[e];
+    if (mine[4] && mine[5] && mine[6] && mine[7])
+      *reinterpret_cast<uint4*>(dst + p + 4) = make_uint4(out[4], out[5], out[6], out[7]);
+    else
+#pragma unroll
+      for (int e = 4; e < kLocItems; ++e)
+        if (mine[e]) dst[p + e] = out[e];
+    __syncthreads();
+  };
   // ---- sort 1: keys -> A(i)
-  block_sort_dominance(S, k, w);
+  block_sort_dominance<kLogB, kUni>(S, k, w);
+  bool mine[kLocItems];
 #pragma unroll
   for (int e = 0; e < kLocItems; ++e) {
     const uint32_t s = t * kLocItems + e, sp = pd(s);
-    const uint32_t i = S.idx[sp];
-    const uint32_t kk = S.v[sp];
-    if (i < nb && kk != 0u) {
-      const uint32_t wi = S.pw[sp] - (s ? S.pw[pd(s - 1)] : 0u);
-      const uint32_t p = kk - 1u;
-      uint32_t d = wi + S.acc[sp];
-      if ((uint64_t)p >= base) d -= P[pd((uint32_t)(p - base))];
-      partial[base + i] = d;
+    const uint32_t kk = S.v[sp], tag = S.tag[sp];
+    const uint32_t i = tag & (kB - 1);
+    at[e] = i;
+    mine[e] = s < nb && k[e] != 0u;
+    uint32_t d = 0;
+    if (kk != 0u) {
+      const bool here = (uint64_t)kk > base && kk != kSentinel;  // p = kk - 1 lies in the block
+      if (kUni) {
+        d = (1u + (tag >> 13) - (here ? (uint32_t)(kk - base) : 0u)) * w0;
+      } else {
+        d = S.pw[sp] - (s ? S.pw[pd(s - 1)] : 0u) + S.acc[sp];
+        if (here) d -= P[pd((uint32_t)(kk - 1 - base))];
+      }
     }
+    out[e] = d;
   }
-  // Cnt_X(p) - Wloc(p) for positions whose next access is in a later block
-  uint32_t ev[kLocItems];
-#pragma unroll
-  for (int e = 0; e < kLocItems; ++e) {
-    const uint32_t lp = t * kLocItems + e;
-    ev[e] = 0;
-    if (lp < nb && nx[e] != kNone && (nx[e] >> kSdLogB) > X) {
-      const uint32_t p = (uint32_t)(base + lp);
-      const uint32_t ub = upper_bound_pd(S.v, 0u, kSdB, p);
-      ev[e] = (ub ? S.pw[pd(ub - 1)] : 0u) - P[pd(lp)];
-    }
-  }
-  __syncthreads();
-  // ---- sort 2: (block of next access, reversed position) -> C(p)
+  put(partial, mine);
+  // ---- sort 2: (block of next access, reversed position) -> N(p)
   uint32_t v2[kLocItems];
 #pragma unroll
   for (int e = 0; e < kLocItems; ++e) {
     const uint32_t lp = t * kLocItems + e;
-    const uint32_t nbk = (nx[e] == kNone) ? G : (nx[e] >> kSdLogB);
-    v2[e] = (lp < nb) ? ((nbk << kSdLogB) | (kSdB - 1u - lp)) : kSentinel;
+    const uint32_t nbk = (nx[e] == kNone) ? G : (nx[e] >> kLogB);
+    v2[e] = (lp < nb) ? ((nbk << kLogB) | (kB - 1u - lp)) : kSentinel;
+    mine[e] = lp < nb && nx[e] != kNone && (nx[e] >> kLogB) > X;
   }
-  block_sort_dominance(S, v2, w);
+  block_sort_dominance<kLogB, kUni>(S, v2, w);
 #pragma unroll
   for (int e = 0; e < kLocItems; ++e) {
-    const uint32_t s = pd(t * kLocItems + e);
-    const uint32_t i = S.idx[s];
-    if (i < nb) P[pd(i)] = S.acc[s];
+    const uint32_t sp = pd(t * kLocItems + e), tag = S.tag[sp];
+    const uint32_t i = tag & (kB - 1);
+    at[e] = i;
+    out[e] = kUni ? (below - (i + 1) + (tag >> 13)) * w0 : below - P[pd(i)] + S.acc[sp];
   }
-  __syncthreads();
-#pragma unroll
-  for (int e = 0; e < kLocItems; ++e) {
-    const uint32_t lp = t * kLocItems + e;
-    if (lp < nb && nx[e] != kNone && (nx[e] >> kSdLogB) > X)
-      E[base + lp] = ev[e] + (P[pd(lp)] - sn[e]);
-  }
+  put(E, mine);
 }
 
 // ---------------------------------------------------------------------------
@@ -386,7 +433,7 @@ template <bool kLds>
 __global__ __launch_bounds__(kAsmNT) void k_sd_assemble(const uint32_t* __restrict__ key,
                                                      const uint8_t* __restrict__ w8,
                                                      const uint8_t* __restrict__ g8, uint64_t n,
-                                                     uint32_t G,
+                                                     uint32_t logb, uint32_t G,
                                                      const uint32_t* __restrict__ partial,
                                                      const uint32_t* __restrict__ E,
                                                      const uint32_t* __restrict__ RQ,
@@ -407,8 +454,8 @@ __global__ __launch_bounds__(kAsmNT) void k_sd_assemble(const uint32_t* __restri
   }
   __syncthreads();
   for (uint32_t X = blockIdx.x; X < G; X += gridDim.x) {
-    const uint64_t base = (uint64_t)X * kSdB;
-    const uint32_t nb = (uint32_t)min<uint64_t>(kSdB, n - base);
+    const uint64_t base = (uint64_t)X << logb;
+    const uint32_t nb = (uint32_t)min<uint64_t>(1ull << logb, n - base);
     const uint64_t row = X >= 2 ? tri_off(X - 1) : 0;
     for (uint32_t j = threadIdx.x; j < nb; j += kAsmNT) {
       const uint64_t i = base + j;
@@ -419,7 +466,7 @@ __global__ __launch_bounds__(kAsmNT) void k_sd_assemble(const uint32_t* __restri
         continue;
       }
       const uint32_t p = kk - 1u;
-      const uint32_t Pb = p >> kSdLogB;
+      const uint32_t Pb = p >> logb;
       uint32_t d = partial[i];
       if (Pb < X) {
         d += E[p];
@@ -792,7 +839,8 @@ __global__ void k_hist_cum(uint64_t* hist, const uint32_t* __restrict__ off, uin
 
 // Test hooks, read at every call: KVCFG_TEST_ROW_CHUNK narrows the LDS
 // histogram of a block-matrix row (so that short traces take the
-// column-chunk path of long ones); KVCFG_TEST_THR_LDS lowers the number of
+// column-chunk path of long ones); KVCFG_TEST_BLOCK_LOG sets the size of the
+// position blocks; KVCFG_TEST_THR_LDS lowers the number of
 // thresholds binned in LDS (so that few thresholds take the global-atomic
 // path of very many).  Both only select among paths of the same result.
 uint32_t env_limit(const char* name, uint32_t dflt, uint32_t lo) {
@@ -808,13 +856,26 @@ uint32_t grid_of(uint64_t m, uint32_t cap = 32768) {
   return (uint32_t)(g ? g : 1);
 }
 
+// log2 of the position block.  Small blocks sort in fewer merge levels, and
+// more of them fit a compute unit and run at once; the block matrix grows
+// with the square of their number.  Matrix and in-block kernels, us, for
+// blocks of 1,024 / 2,048 / 4,096 / 8,192: 238,313 accesses 68 / 67 / 70 / 87;
+// 4.6e6: 214 / 181 / 189 / 228; 1.09e8: 24,780 / 8,740 / 4,380 / 3,560.
+uint32_t block_log(uint64_t n) {
+  if (const char* e = std::getenv("KVCFG_TEST_BLOCK_LOG"))
+    return (uint32_t)std::min(13ul, std::max(10ul, std::strtoul(e, nullptr, 10)));
+  return n <= (1ull << 18) ? 10 : n <= (1ull << 23) ? 11 : n <= (1ull << 25) ? 12 : 13;
+}
+
 }  // namespace
 
 kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& ts,
                      const uint32_t* thr_dev, const uint32_t* off_dev, uint64_t* hist,
                      uint64_t* phist, const JointArgs* ja, const uint8_t* real, hipStream_t s) {
   const uint64_t n = o.n ? o.n : t.n;
-  const uint32_t G = div_up(n, kSdB);
+  const uint32_t logb = block_log(n);
+  const uint32_t G = div_up(n, 1u << logb);
+  const bool uni = t.st.w_min == t.st.w_max;
   kv_status st;
   const uint64_t tri = G >= 2 ? tri_off(G) : 1;
   const uint32_t nchunks = div_up(G, kColRows);
@@ -849,7 +910,7 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
   if (G >= 2) {
     StageTimer tm(kStStackMatrix, s);
     const uint32_t row_chunk = env_limit("KVCFG_TEST_ROW_CHUNK", kRowChunk, 1);
-    hipLaunchKernelGGL(k_sd_rowhist, dim3(G), dim3(kRowNT), 0, s, key, w8, n, row_chunk, Q);
+    hipLaunchKernelGGL(k_sd_rowhist, dim3(G), dim3(kRowNT), 0, s, key, w8, n, logb, row_chunk, Q);
     KV_HIP(hipGetLastError());
     const dim3 cg(div_up(G, 256), nchunks);
     hipLaunchKernelGGL(k_sd_colsum, cg, dim3(256), 0, s, Q, G, b_csum.as<uint32_t>());
@@ -863,8 +924,16 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
   }
   {
     StageTimer tm(kStStackLocal, s);
-    hipLaunchKernelGGL(k_sd_local, dim3(G), dim3(kLocNT), 0, s, key, nxt, w8, n, G,
-                       b_partial.as<uint32_t>(), b_E.as<uint32_t>());
+    const auto local = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3(G), dim3((1u << logb) / kLocItems), 0, s, key, nxt, w8,
+                         t.st.w_max, n, G, b_partial.as<uint32_t>(), b_E.as<uint32_t>());
+    };
+    switch (logb) {
+      case 10: uni ? local(k_sd_local<10, true>) : local(k_sd_local<10, false>); break;
+      case 11: uni ? local(k_sd_local<11, true>) : local(k_sd_local<11, false>); break;
+      case 12: uni ? local(k_sd_local<12, true>) : local(k_sd_local<12, false>); break;
+      default: uni ? local(k_sd_local<13, true>) : local(k_sd_local<13, false>);
+    }
     KV_HIP(hipGetLastError());
   }
   BinArgs ba{thr_dev, off_dev, (uint32_t)ts.values.size(), ts.n_groups, hist};
@@ -879,11 +948,11 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
   {
   StageTimer tm(kStStackAssemble, s);
   if (lds)
-    hipLaunchKernelGGL(k_sd_assemble<true>, dim3(ga), dim3(kAsmNT), 0, s, key, w8, g8, n, G,
+    hipLaunchKernelGGL(k_sd_assemble<true>, dim3(ga), dim3(kAsmNT), 0, s, key, w8, g8, n, logb, G,
                        (const uint32_t*)b_partial.as<uint32_t>(),
                        (const uint32_t*)b_E.as<uint32_t>(), (const uint32_t*)Q, ba, dist, real);
   else
-    hipLaunchKernelGGL(k_sd_assemble<false>, dim3(ga), dim3(kAsmNT), 0, s, key, w8, g8, n, G,
+    hipLaunchKernelGGL(k_sd_assemble<false>, dim3(ga), dim3(kAsmNT), 0, s, key, w8, g8, n, logb, G,
                        (const uint32_t*)b_partial.as<uint32_t>(),
                        (const uint32_t*)b_E.as<uint32_t>(), (const uint32_t*)Q, ba, dist, real);
   KV_HIP(hipGetLastError());

@@ -14,8 +14,6 @@
 namespace kv {
 
 constexpr uint32_t kNone = 0xFFFFFFFFu;
-constexpr int kSdLogB = 13;                 // stack-distance position block: 8192
-constexpr uint32_t kSdB = 1u << kSdLogB;
 constexpr uint64_t kMaxN = 1ull << 29;
 
 // ---------------------------------------------------------------------------
