@@ -85,6 +85,8 @@ constexpr uint32_t kCand = 4096;           // LFU eviction candidates per chunk
 constexpr int kCScan = 2;                  // candidate positions per thread and pass
 constexpr uint32_t kMinFast = 256;         // shorter LFU chunks go serial
 constexpr uint32_t kHeadLds = 64;          // class heads held in LDS during a serial walk
+constexpr uint32_t kFarSearch = 4096;      // positions one wavefront searches for a victim
+constexpr int kSearchIt = 16;              // positions per thread and step of the block's search
 constexpr uint16_t kInf16 = 0xFFFF;
 constexpr int kLfuNT = 1024;               // threads of an LFU replay workgroup
 constexpr uint32_t kLChunk = 4096;         // longest LFU chunk
@@ -625,6 +627,11 @@ struct LfuLds {
   uint64_t vw;                // candidate scan: untouched weight found
   int ok;
   uint32_t evn;               // evictions so far (emitting launches, after a serial walk)
+  // a serial walk that stopped for a long victim search: the access it
+  // stopped at, its hit word so far, and where the search goes on; the
+  // search's finds, alternating between its steps
+  uint32_t si, sfrom, sfound[2];
+  uint64_t sword;
   // per access of the chunk (local position).  Members of one union serve
   // the fixed point and the apply step respectively, never both at once.
   union {
@@ -783,10 +790,12 @@ __device__ __forceinline__ void lfu_serial_stage(const JobDev& j, const JobArgs&
 // Exact replay of the staged [p0, p1) by the 64 lanes of one wavefront.
 // Every lane holds the same state and applies the same updates (stores of
 // equal values to one address); only the victim search spreads candidate
-// positions over the lanes.  Returns false if the state is found
-// inconsistent.
+// positions over the lanes.  A search that passes kFarSearch positions is
+// left to the block (lfu_search): the walk stops before its access (S.si) and
+// is called again.  Returns kSerialBad if the state is found inconsistent.
+enum : int { kSerialBad = 0, kSerialDone = 1, kSerialSearch = 2 };
 template <bool kEmit>
-__device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& a,
+__device__ __forceinline__ int lfu_serial_wave(const JobDev& j, const JobArgs& a,
                                                 uint32_t* __restrict__ cnt, uint32_t* head,
                                                 uint32_t n_class, const Classes& cl, LfuLds& S,
                                                 GroupCounters& gc, uint64_t* __restrict__ bits,
@@ -798,9 +807,9 @@ __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& 
   uint32_t head1 = head1_io;
   uint64_t used = used_io;
   uint32_t fmin = S.fmin;
-  uint64_t word = 0;
-  bool ok = true;
-  for (uint32_t i = p0; i < p1 && ok; ++i) {
+  uint64_t word = S.sword;
+  int ok = kSerialDone;
+  for (uint32_t i = S.si; i < p1 && ok == kSerialDone; ++i) {
     const uint32_t x = i - p0;
     if (i >= b0) {
       const uint32_t w = S.sw[x];
@@ -827,6 +836,15 @@ __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& 
           if (fmin < kTopClass) {
             const uint32_t h0 = fmin == 1 ? head1 : (fmin < kHeadLds ? S.shead[fmin] : head[fmin]);
             for (uint32_t base = h0; base < i; base += 64) {
+              if (base - h0 >= kFarSearch && base < p0) {  // none of the class before base
+                if (lane == 0) {
+                  S.si = i;
+                  S.sfrom = base;
+                  S.sword = word;
+                }
+                ok = kSerialSearch;
+                break;
+              }
               const uint32_t r = base + lane;
               uint32_t c = 0, nr = kNone, wr = 0, gr = 0;
               if (r < i) {
@@ -870,8 +888,9 @@ __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& 
               vg = q >= p0 ? S.sg[q - p0] : a.g8[o][q];
             }
           }
+          if (ok == kSerialSearch) break;
           if (q >= i) {
-            ok = false;
+            ok = kSerialBad;
             break;
           }
           if (fmin == 1) head1 = q + 1;
@@ -891,6 +910,7 @@ __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& 
             if (nf != 0xFFFFFFFFu) fmin = nf;
           }
         }
+        if (ok != kSerialDone) break;
         S.scnt[x] = 1;
         cnt[i - b0] = 1;
         class_add1(cl, 1, +1);
@@ -911,6 +931,59 @@ __device__ __forceinline__ bool lfu_serial_wave(const JobDev& j, const JobArgs& 
   used_io = used;
   head1_io = head1;
   return ok;
+}
+
+// The serial walk's victim search, by the whole block: the first live member
+// of class S.fmin from S.sfrom on, among the positions before p0 (the walk
+// looks through the rest).  The class's head moves there.  A class of two or
+// more touches can have its oldest member hundreds of millions of positions
+// back, or none before p0: one wavefront took 0.8 s for such a search over
+// 3.9e8 positions, and a replay 4.4 s for four of them instead of 1.35 s;
+// the block streams the counts with kSearchIt loads in flight per thread.
+// Out of line: inlined, it cost the fast chunks 6% in spilled registers.
+template <int NT>
+__device__ __attribute__((noinline)) void lfu_search(const uint32_t* __restrict__ cnt,
+                                                     const uint32_t* __restrict__ nxt,
+                                                     uint32_t* head, LfuLds& S, uint32_t b0,
+                                                     uint32_t p0) {
+  const uint32_t tid = threadIdx.x;
+  if (tid < 2) S.sfound[tid] = kNone;
+  __syncthreads();
+  const uint32_t f = S.fmin, i = S.si, end = min(i, p0);
+  uint32_t h = S.sfrom, to = end;
+  for (uint32_t step = 0; h < end; ++step) {
+    uint32_t c[kSearchIt];
+#pragma unroll
+    for (int e = 0; e < kSearchIt; ++e) {
+      const uint32_t r = min(h + (uint32_t)e * NT + tid, end - 1);
+      c[e] = cnt[r - b0];
+    }
+    uint32_t best = kNone;
+#pragma unroll
+    for (int e = kSearchIt - 1; e >= 0; --e) {
+      const uint32_t r = h + (uint32_t)e * NT + tid;
+      if (r >= end || c[e] != f) continue;
+      const uint32_t nr = nxt[r];
+      if (nr == kNone || nr >= i) best = r;
+    }
+    if (best != kNone) atomicMin(&S.sfound[step & 1], best);
+    __syncthreads();
+    const uint32_t q = S.sfound[step & 1];
+    if (q != kNone) {
+      to = q;
+      break;
+    }
+    h += NT * kSearchIt;
+  }
+  if (tid == 0) {
+    if (f == 1) {
+      S.head1 = to;
+    } else {
+      if (f < kHeadLds) S.shead[f] = to;
+      head[f] = to;
+    }
+  }
+  __syncthreads();
 }
 
 constexpr int kWin = 8;                           // demands searched in registers
@@ -1710,22 +1783,31 @@ __device__ __forceinline__ void lfu_chunked(const JobDev& j, const JobArgs& a,
       __syncthreads();
       class_bits_rebuild<NT>(S);
       lfu_serial_stage<NT>(j, a, cnt, head, a.n_class, S, (uint32_t)pos, (uint32_t)(pos + l));
-      __syncthreads();
-      if (wave_id() == 0) {
-        const bool ok = lfu_serial_wave<kEmit>(j, a, cnt, head, a.n_class, cl, S, gc, bits,
-                                               (uint32_t)pos, (uint32_t)(pos + l), used, head1,
-                                               evn);
-        if (lane_id() == 0) {
-          if constexpr (kEmit) S.evn = evn;
-          S.ok = ok ? 1 : 0;
-          S.used = used;
-          S.head1 = head1;
-        }
+      if (tid == 0) {
+        S.si = (uint32_t)pos;
+        S.sword = 0;
       }
       __syncthreads();
-      used = S.used;
-      head1 = S.head1;
-      if constexpr (kEmit) evn = S.evn;
+      for (;;) {
+        if (wave_id() == 0) {
+          const int ok = lfu_serial_wave<kEmit>(j, a, cnt, head, a.n_class, cl, S, gc, bits,
+                                                 (uint32_t)pos, (uint32_t)(pos + l), used, head1,
+                                                 evn);
+          if (lane_id() == 0) {
+            if constexpr (kEmit) S.evn = evn;
+            S.ok = ok;
+            S.used = used;
+            S.head1 = head1;
+          }
+        }
+        __syncthreads();
+        used = S.used;
+        head1 = S.head1;
+        if constexpr (kEmit) evn = S.evn;
+        if (S.ok != kSerialSearch) break;
+        lfu_search<NT>(cnt, a.nxt[j.order], head, S, (uint32_t)j.begin, (uint32_t)pos);
+        head1 = S.head1;
+      }
       if (!S.ok) break;
       pos += l;
       ppos = ~0ull;
