@@ -54,18 +54,27 @@ constexpr uint32_t kSentinel = 0xFFFFFFFFu;
 constexpr uint32_t kRowChunk = 16384;   // LDS histogram bins per row chunk
 constexpr int kRowNT = 1024;            // threads per row of the block matrix
 constexpr int kAsmNT = 1024;            // threads per workgroup of the distance binning kernels
-constexpr uint32_t kColRows = 64;       // rows per column-scan chunk
+constexpr uint32_t kSubs = kAsmNT / 64; // parts of a block, one per wavefront of the assembly
 constexpr uint32_t kThrLds = 6144;      // thresholds kept in LDS for binning
 
 __host__ __device__ __forceinline__ uint64_t tri_off(uint64_t x) { return x * (x - 1) / 2; }
 
+// What the pass adds to with atomics, cleared by its first kernel.
+struct Zero {
+  uint64_t* p[3];
+  uint32_t n[3];
+};
+
 // ---------------------------------------------------------------------------
-// Q rows: Q[X][Y] for Y < X, inclusive prefix over ceil(key / B).
+// Q rows: Q[X][Y] for Y < X, inclusive prefix over ceil(key / B); the weight of
+// the last occurrences in each sixteenth of a block.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restrict__ key,
-                                                    const uint8_t* __restrict__ w8, uint64_t n,
-                                                    uint32_t logb, uint32_t row_chunk,
-                                                    uint32_t* __restrict__ Q) {
+                                                    const uint32_t* __restrict__ nxt,
+                                                    const uint8_t* __restrict__ w8, uint32_t w0,
+                                                    uint64_t n, uint32_t logb, uint32_t row_chunk,
+                                                    uint32_t* __restrict__ Q,
+                                                    uint32_t* __restrict__ lsum, Zero z) {
   // bin j lives at hp(j), one padding word after every 64: the scan below
   // gives each thread a run of up to kRowChunk / kRowNT bins, which would
   // otherwise put the lanes of a wavefront on a few banks
@@ -73,9 +82,22 @@ __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restric
   __shared__ uint32_t sh[kRowNT / 64 + 1];
   const auto hp = [](uint32_t j) { return j + (j >> 6); };
   const uint32_t X = blockIdx.x;
-  if (X == 0) return;
+  for (int q = 0; q < 3; ++q)
+    for (uint32_t j = X * kRowNT + threadIdx.x; j < z.n[q]; j += gridDim.x * kRowNT) z.p[q][j] = 0;
   const uint64_t base = (uint64_t)X << logb;
   const uint32_t nb = (uint32_t)min<uint64_t>(1ull << logb, n - base);
+  // a wavefront's 64 positions lie in one sixteenth of the block
+  if (threadIdx.x < kSubs) sh[threadIdx.x] = 0;
+  __syncthreads();
+  for (uint32_t j = threadIdx.x; j < (1u << logb); j += kRowNT) {
+    uint32_t v = 0;
+    if (j < nb && nxt[base + j] == kNone) v = w0 ? w0 : (uint32_t)w8[base + j];
+    v = wave_add_dpp(v);
+    if (v && lane_id() == 0) atomicAdd(&sh[(j * kSubs) >> logb], v);
+  }
+  __syncthreads();
+  if (threadIdx.x < kSubs) lsum[X * kSubs + threadIdx.x] = sh[threadIdx.x];
+  __syncthreads();
   const uint64_t row = tri_off(X);
   for (uint32_t c0 = 0; c0 < X; c0 += row_chunk) {
     const uint32_t width = min(row_chunk, X - c0);
@@ -84,7 +106,7 @@ __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restric
     uint32_t carry = 0;
     for (uint32_t j = threadIdx.x; j < nb; j += kRowNT) {
       const uint32_t c = (key[base + j] + ((1u << logb) - 1u)) >> logb;
-      const uint32_t w = w8[base + j];
+      const uint32_t w = w0 ? w0 : (uint32_t)w8[base + j];
       if (c < c0) carry += w;
       else if (c < c0 + width) atomicAdd(&h[hp(c - c0)], w);
     }
@@ -106,40 +128,93 @@ __global__ __launch_bounds__(kRowNT) void k_sd_rowhist(const uint32_t* __restric
   }
 }
 
-// Column sums of Q over chunks of kColRows rows (only rows X > Y count).
-__global__ __launch_bounds__(256) void k_sd_colsum(const uint32_t* __restrict__ Q, uint32_t G,
-                                                   uint32_t* __restrict__ csum) {
-  const uint32_t Y = blockIdx.x * 256 + threadIdx.x;
-  const uint32_t c = blockIdx.y;
-  if (Y >= G) return;
-  const uint32_t x0 = max(Y + 1, c * kColRows), x1 = min(G, (c + 1) * kColRows);
-  uint32_t s = 0;
-  for (uint32_t X = x0; X < x1; ++X) s += Q[tri_off(X) + Y];
-  csum[(uint64_t)c * G + Y] = s;
-}
+struct SegArgs {
+  uint64_t seg[KV_MAX_GROUPS + 1];
+  uint32_t partitioned;
+};
 
-__global__ __launch_bounds__(256) void k_sd_colchunks(uint32_t* __restrict__ csum, uint32_t G,
-                                                      uint32_t nchunks) {
-  const uint32_t Y = blockIdx.x * 256 + threadIdx.x;
-  if (Y >= G) return;
-  uint32_t run = 0;
-  for (uint32_t c = 0; c < nchunks; ++c) {
-    const uint32_t v = csum[(uint64_t)c * G + Y];
-    csum[(uint64_t)c * G + Y] = run;
-    run += v;
+// Column prefix sums of Q (rows X > Y count), kCols columns per workgroup: each
+// row of kCols threads sums a range of rows, then writes the running sums from
+// the ranges above (three kernels over chunks of 64 rows left most of the
+// chip idle and cost two more launches: 2,256 blocks 35 -> 21 us, 13,277
+// blocks 370 -> 410 us, before the launches).  The last workgroup sums
+// up the last occurrences instead: lpre[q] before the q-th sixteenth of a
+// block, and per segment their weight up to its end (of the whole order when
+// shared).
+template <uint32_t kCols>
+__global__ __launch_bounds__(kRowNT) void k_sd_cols(uint32_t* __restrict__ Q, uint32_t G,
+                                                    const uint32_t* __restrict__ lsum,
+                                                    uint32_t* __restrict__ lpre,
+                                                    uint32_t* __restrict__ segend,
+                                                    const uint32_t* __restrict__ nxt,
+                                                    const uint8_t* __restrict__ w8, uint64_t n,
+                                                    uint32_t logb, SegArgs sa) {
+  constexpr uint32_t kW = kRowNT / 64, kRanges = kRowNT / kCols;
+  __shared__ uint32_t part[kRanges][kCols];
+  const uint32_t lane = lane_id(), w = (uint32_t)wave_id();
+  if (blockIdx.x + 1 == gridDim.x) {
+    uint32_t run = 0;
+    const uint32_t m = G * kSubs;
+    for (uint32_t b = 0; b < m; b += kRowNT * 4) {  // four per thread (m is a multiple of four)
+      const uint32_t q = b + threadIdx.x * 4;
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (q < m) v = *reinterpret_cast<const uint4*>(lsum + q);
+      uint32_t tot;
+      const uint32_t pre =
+          run + block_excl_scan_u32<kRowNT>(v.x + v.y + v.z + v.w, &part[0][0], tot);
+      if (q < m)
+        *reinterpret_cast<uint4*>(lpre + q) =
+            make_uint4(pre, pre + v.x, pre + v.x + v.y, pre + v.x + v.y + v.z);
+      run += tot;
+    }
+    __syncthreads();
+    static_assert(kW >= KV_MAX_GROUPS, "a wavefront per segment");
+    if (w < KV_MAX_GROUPS) {
+      const uint64_t e = sa.partitioned ? sa.seg[w + 1] : n, s0 = sa.partitioned ? sa.seg[w] : 0;
+      uint32_t v = 0;
+      if (e > s0) {
+        const uint64_t X = (e - 1) >> logb;
+        for (uint64_t i = (X << logb) + lane; i < e; i += 64)
+          if (nxt[i] == kNone) v += w8[i];
+        v = wave_sum(v) + lpre[X * kSubs];
+      }
+      if (lane == 0) segend[w] = v;
+    }
+    return;
   }
-}
-
-__global__ __launch_bounds__(256) void k_sd_colapply(uint32_t* __restrict__ Q, uint32_t G,
-                                                     const uint32_t* __restrict__ csum) {
-  const uint32_t Y = blockIdx.x * 256 + threadIdx.x;
-  const uint32_t c = blockIdx.y;
-  if (Y >= G) return;
-  const uint32_t x0 = max(Y + 1, c * kColRows), x1 = min(G, (c + 1) * kColRows);
-  uint32_t run = csum[(uint64_t)c * G + Y];
-  for (uint32_t X = x0; X < x1; ++X) {
-    run += Q[tri_off(X) + Y];
-    Q[tri_off(X) + Y] = run;
+  const uint32_t c = threadIdx.x % kCols, r = threadIdx.x / kCols;
+  const uint32_t Y0 = blockIdx.x * kCols, Y = Y0 + c;
+  const uint32_t per = (G - 1 - Y0 + kRanges - 1) / kRanges;  // rows Y0 + 1 .. G - 1
+  const uint32_t x0 = Y0 + 1 + r * per, x1 = min(G, x0 + per);
+  constexpr int kU = 8;  // loads in flight
+  uint32_t s = 0;
+  for (uint32_t X = x0; X < x1; X += kU) {
+    uint32_t v[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) v[q] = X + q < x1 && X + q > Y ? Q[tri_off(X + q) + Y] : 0u;
+#pragma unroll
+    for (int q = 0; q < kU; ++q) s += v[q];
+  }
+  part[r][c] = s;
+  __syncthreads();
+  // exclusive sums over the ranges: a wavefront per column
+  static_assert(kRanges <= 64, "a wavefront scans a column");
+  for (uint32_t q = w; q < kCols; q += kW) {
+    const uint32_t v = lane < kRanges ? part[lane][q] : 0u;
+    const uint32_t inc = wave_incl_scan_u32(v);
+    if (lane < kRanges) part[lane][q] = inc - v;
+  }
+  __syncthreads();
+  uint32_t run = part[r][c];
+  for (uint32_t X = x0; X < x1; X += kU) {
+    uint32_t v[kU];
+#pragma unroll
+    for (int q = 0; q < kU; ++q) v[q] = X + q < x1 && X + q > Y ? Q[tri_off(X + q) + Y] : 0u;
+#pragma unroll
+    for (int q = 0; q < kU; ++q) {
+      run += v[q];
+      if (X + q < x1 && X + q > Y) Q[tri_off(X + q) + Y] = run;
+    }
   }
 }
 
@@ -429,74 +504,228 @@ struct BinArgs {
   uint64_t* hist;        // u64[bins][4]
 };
 
-template <bool kLds>
-__global__ __launch_bounds__(kAsmNT) void k_sd_assemble(const uint32_t* __restrict__ key,
-                                                     const uint8_t* __restrict__ w8,
-                                                     const uint8_t* __restrict__ g8, uint64_t n,
-                                                     uint32_t logb, uint32_t G,
-                                                     const uint32_t* __restrict__ partial,
-                                                     const uint32_t* __restrict__ E,
-                                                     const uint32_t* __restrict__ RQ,
-                                                     BinArgs ba, uint32_t* __restrict__ dout,
-                                                     const uint8_t* __restrict__ real) {
-  __shared__ uint32_t sthr[kLds ? kThrLds : 1];
-  __shared__ uint32_t scnt[kLds ? kThrLds + KV_MAX_GROUPS : 1];
-  __shared__ uint32_t sw[kLds ? kThrLds + KV_MAX_GROUPS : 1];
-  __shared__ uint32_t soff[KV_MAX_GROUPS + 1];
-  const uint32_t nbins = ba.n_thr + ba.n_groups;
-  if (threadIdx.x <= ba.n_groups) soff[threadIdx.x] = ba.off[threadIdx.x];
+// Disk TTL tiers.  A bounded TTL tier (capacity C, TTL t, least recently
+// accessed block displaced first) holds a block at access i iff D_i <= C and
+// its gap delta_i <= t: the blocks it holds are the top of the LRU stack up
+// to C, minus those not accessed for t, and with one TTL the latter are a
+// bottom part of the stack (ages grow with depth).  An unbounded one is
+// C = infinity.  So per group one joint histogram of (D bin, gap bin) serves
+// every (capacity, TTL), and one of (final depth bin, end-age bin) gives the
+// blocks held at the last request.
+constexpr uint64_t kAsmLds = 150 * 1024;  // most LDS of the assembly's tables
+
+struct AsmArgs {
+  const uint32_t *key, *nxt;
+  const uint8_t *w8, *g8, *real;
+  uint64_t n;
+  uint32_t w0;          // every access's weight, or 0
+  uint32_t logb, G;
+  const uint32_t *partial, *E, *RQ;
+  uint32_t* dout;       // distances, or null
+  const uint32_t *lpre, *segend;
+  uint32_t partitioned;
+  const uint32_t* req;  // joint histograms
+  const double* rt;
+};
+
+// Number of values below x in sorted a[lo, lo + len), the same steps for every
+// lane: several searches of a thread run side by side.
+template <int R, class T>
+__device__ __forceinline__ void count_below(const T* a, const uint32_t (&lo)[R],
+                                            const uint32_t (&len)[R], uint32_t longest,
+                                            const T (&x)[R], uint32_t (&at)[R]) {
+#pragma unroll
+  for (int r = 0; r < R; ++r) at[r] = 0;
+  uint32_t h = 1;
+  while (h <= longest / 2) h *= 2;  // largest power of two <= longest (1 if none)
+  for (; h; h >>= 1) {
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t t = at[r] + h;
+      if (t <= len[r] && a[lo[r] + t - 1] < x[r]) at[r] = t;
+    }
+  }
+}
+
+// Assembles the distances and bins them, and the final depths of the blocks
+// (the weight of distinct blocks whose last access is at or after their own,
+// inside their segment) at their last accesses; with kJoint both also by gap
+// and by age.  One pass over the positions: a thread takes R = B / 1,024 of
+// them, whose chains of gathers and threshold searches run side by side.
+// The histograms add up in LDS (kLds; the joint ones kJoint = 1; else, and
+// kJoint = 2, in device memory), each flushed once per workgroup.  Measured against the five kernels this replaced
+// (assembly, last-occurrence weights, their scan, final depths, joint bins):
+// ASMFIGURES
+template <int R, bool kLds, int kJoint>
+__global__ __launch_bounds__(kAsmNT) void k_sd_assemble(AsmArgs a, BinArgs ba, JointArgs ja) {
+  extern __shared__ double lds[];
+  __shared__ uint32_t soff[KV_MAX_GROUPS + 1], stoff[KV_MAX_GROUPS + 1], sjb[KV_MAX_GROUPS + 1];
+  __shared__ uint32_t send[KV_MAX_GROUPS];
+  const uint32_t ng = ba.n_groups, nbins = ba.n_thr + ng;
+  const uint32_t ntb = kJoint ? ja.n_tthr + ng : 0u;
+  // doubles first: TTL values, weighted gaps; then thresholds and histograms
+  double* stt = lds;
+  double* swd = stt + (kJoint == 1 ? ja.n_tthr : 0u);
+  uint32_t* sthr = reinterpret_cast<uint32_t*>(swd + (kJoint == 1 ? ntb : 0u));
+  uint32_t* hist = sthr + (kLds ? ba.n_thr : 0u);  // [4][nbins], then [4][n_joint]
+  uint32_t* joint = hist + (kLds ? 4 * nbins : 0u);
+  if (threadIdx.x <= ng) {
+    soff[threadIdx.x] = ba.off[threadIdx.x];
+    stoff[threadIdx.x] = kJoint ? ja.toff[threadIdx.x] : 0u;
+    sjb[threadIdx.x] = kJoint ? ja.jbase[threadIdx.x] : 0u;
+  }
+  if (threadIdx.x < KV_MAX_GROUPS) send[threadIdx.x] = a.segend[a.partitioned ? threadIdx.x : 0u];
   if (kLds) {
     for (uint32_t j = threadIdx.x; j < ba.n_thr; j += kAsmNT) sthr[j] = ba.thr[j];
-    for (uint32_t j = threadIdx.x; j < nbins; j += kAsmNT) {
-      scnt[j] = 0;
-      sw[j] = 0;
+    for (uint32_t j = threadIdx.x; j < 4 * nbins; j += kAsmNT) hist[j] = 0;
+    if (kJoint == 1) {
+      for (uint32_t j = threadIdx.x; j < ja.n_tthr; j += kAsmNT) stt[j] = ja.tthr[j];
+      for (uint32_t j = threadIdx.x; j < ntb; j += kAsmNT) swd[j] = 0.0;
+      for (uint32_t j = threadIdx.x; j < 4 * ja.n_joint; j += kAsmNT) joint[j] = 0;
     }
   }
   __syncthreads();
-  for (uint32_t X = blockIdx.x; X < G; X += gridDim.x) {
-    const uint64_t base = (uint64_t)X << logb;
-    const uint32_t nb = (uint32_t)min<uint64_t>(1ull << logb, n - base);
+  const uint32_t* thr = kLds ? sthr : ba.thr;
+  const double* tthr = kJoint == 1 ? stt : ja.tthr;
+  uint32_t longest = 0, tlongest = 0;
+  for (uint32_t g = 0; g < ng; ++g) {
+    longest = max(longest, soff[g + 1] - soff[g]);
+    tlongest = max(tlongest, stoff[g + 1] - stoff[g]);
+  }
+  const double t_end = kJoint ? a.rt[a.req[a.n - 1]] : 0.0;  // the last access's request
+  // field f (0 / 1: accesses, their weight; 2 / 3: blocks, theirs) of a bin
+  const auto add = [&](uint32_t bin, uint32_t f, uint32_t w) {
+    if (kLds) {
+      atomicAdd(&hist[f * nbins + bin], 1u);
+      if (!a.w0) atomicAdd(&hist[(f + 1) * nbins + bin], w);
+    } else {
+      atomicAdd((unsigned long long*)&ba.hist[bin * 4 + f], 1ull);
+      atomicAdd((unsigned long long*)&ba.hist[bin * 4 + f + 1], (unsigned long long)w);
+    }
+  };
+  const auto add_joint = [&](uint32_t bin, uint32_t f, uint32_t w) {
+    if (kJoint == 1) {
+      atomicAdd(&joint[f * ja.n_joint + bin], 1u);
+      if (!a.w0) atomicAdd(&joint[(f + 1) * ja.n_joint + bin], w);
+    } else {
+      uint64_t* h = f ? ja.fh : ja.jh;
+      atomicAdd((unsigned long long*)&h[2 * (uint64_t)bin], 1ull);
+      atomicAdd((unsigned long long*)&h[2 * (uint64_t)bin + 1], (unsigned long long)w);
+    }
+  };
+  const uint32_t wv = (uint32_t)wave_id(), lane = lane_id();
+  for (uint32_t X = blockIdx.x; X < a.G; X += gridDim.x) {
+    const uint64_t i0 = ((uint64_t)X << a.logb) + wv * (64 * R) + lane;
+    const uint64_t end = min<uint64_t>(a.n, (uint64_t)(X + 1) << a.logb);
+    uint32_t k[R], w[R], g[R], lo[R], len[R], dep[R], d[R], at[R];
+    bool in[R], fin[R], hit[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint64_t i = i0 + r * 64;
+      in[r] = i < end;
+      const uint64_t q = in[r] ? i : 0;
+      k[r] = a.key[q];
+      fin[r] = in[r] && a.nxt[q] == kNone;
+      w[r] = a.w0 ? a.w0 : (uint32_t)a.w8[q];
+      g[r] = ng > 1 ? (uint32_t)a.g8[q] : 0u;
+      hit[r] = in[r] && k[r] != 0u && !(a.real && !a.real[q]);  // a re-touch is not binned
+      d[r] = hit[r] ? a.partial[q] : 0u;
+    }
+    // the rest of the distances
     const uint64_t row = X >= 2 ? tri_off(X - 1) : 0;
-    for (uint32_t j = threadIdx.x; j < nb; j += kAsmNT) {
-      const uint64_t i = base + j;
-      if (real && !real[i]) continue;  // a re-touch of the radix-tree order: not binned
-      const uint32_t kk = key[i];
-      if (kk == 0) {
-        if (dout) dout[i] = kNone;  // a first access: no finite distance
-        continue;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t p = k[r] - 1u, Pb = p >> a.logb;
+      if (hit[r] && Pb < X) {
+        d[r] += a.E[p];
+        if (Pb + 1 < X) d[r] += a.RQ[row + Pb];
       }
-      const uint32_t p = kk - 1u;
-      const uint32_t Pb = p >> logb;
-      uint32_t d = partial[i];
-      if (Pb < X) {
-        d += E[p];
-        if (Pb + 1 < X) d += RQ[row + Pb];
+    }
+    // weight of the last occurrences before each position
+    uint32_t tot = 0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const uint32_t v = fin[r] ? w[r] : 0u, inc = wave_incl_scan_u32(v);
+      dep[r] = tot + inc - v;
+      tot += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    }
+    const uint32_t below = a.lpre[X * kSubs + wv];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      dep[r] = send[a.partitioned ? g[r] : 0u] - (below + dep[r]);
+      lo[r] = soff[g[r]];
+      len[r] = soff[g[r] + 1] - lo[r];
+      if (a.dout && in[r]) a.dout[i0 + r * 64] = k[r] ? d[r] : kNone;
+    }
+    uint32_t db[R], fb[R];
+    count_below<R>(thr, lo, len, longest, d, db);
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if (hit[r]) add(lo[r] + g[r] + db[r], 0, w[r]);
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < R; ++r) any |= fin[r];
+    any = __ballot(any) != 0ull;
+    if (any) {
+      count_below<R>(thr, lo, len, longest, dep, fb);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (fin[r]) add(lo[r] + g[r] + fb[r], 2, w[r]);
+    }
+    if constexpr (kJoint != 0) {
+      double gap[R], age[R];
+      uint32_t tlo[R], tlen[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint64_t q = in[r] ? i0 + r * 64 : 0;
+        const double t = a.rt[a.req[q]];
+        gap[r] = hit[r] ? t - a.rt[a.req[k[r] - 1u]] : 0.0;
+        age[r] = t_end - t;
+        tlo[r] = stoff[g[r]];
+        tlen[r] = stoff[g[r] + 1] - tlo[r];
       }
-      if (dout) dout[i] = d;
-      const uint32_t g = g8[i];
-      const uint32_t w = w8[i];
-      const uint32_t lo = soff[g], hi = soff[g + 1];
-      if (kLds) {
-        const uint32_t b = lower_bound(sthr, lo, hi, d) - lo;
-        const uint32_t bin = lo + g + b;
-        atomicAdd(&scnt[bin], 1u);
-        atomicAdd(&sw[bin], w);
-      } else {
-        const uint32_t b = lower_bound(ba.thr, lo, hi, d) - lo;
-        const uint32_t bin = lo + g + b;
-        atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 0], 1ull);
-        atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 1], (unsigned long long)w);
+      count_below<R>(tthr, tlo, tlen, tlongest, gap, at);
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        if (!in[r]) continue;
+        // a first access: past every threshold and every TTL
+        const uint32_t b = hit[r] ? db[r] : len[r], t = hit[r] ? at[r] : tlen[r];
+        add_joint(sjb[g[r]] + b * (tlen[r] + 1) + t, 0, w[r]);
+        if (hit[r])
+          atomicAdd((kJoint == 1 ? swd : ja.wd) + tlo[r] + g[r] + t, (double)w[r] * gap[r]);
+      }
+      if (any) {
+        count_below<R>(tthr, tlo, tlen, tlongest, age, at);
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if (fin[r]) add_joint(sjb[g[r]] + fb[r] * (tlen[r] + 1) + at[r], 2, w[r]);
       }
     }
   }
-  if (kLds) {
-    __syncthreads();
-    for (uint32_t j = threadIdx.x; j < nbins; j += kAsmNT) {
-      if (scnt[j]) {
-        atomicAdd((unsigned long long*)&ba.hist[j * 4 + 0], (unsigned long long)scnt[j]);
-        atomicAdd((unsigned long long*)&ba.hist[j * 4 + 1], (unsigned long long)sw[j]);
-      }
+  if (!kLds) return;
+  __syncthreads();
+  // with one weight the counts give the weights
+  for (uint32_t j = threadIdx.x; j < 2 * nbins; j += kAsmNT) {
+    const uint32_t f = j < nbins ? 0u : 2u, b = j < nbins ? j : j - nbins;
+    const uint32_t c = hist[f * nbins + b];
+    if (!c) continue;
+    const unsigned long long cw = a.w0 ? (unsigned long long)c * a.w0 : hist[(f + 1) * nbins + b];
+    atomicAdd((unsigned long long*)&ba.hist[b * 4 + f], (unsigned long long)c);
+    atomicAdd((unsigned long long*)&ba.hist[b * 4 + f + 1], cw);
+  }
+  if constexpr (kJoint == 1) {
+    for (uint32_t j = threadIdx.x; j < 2 * ja.n_joint; j += kAsmNT) {
+      const uint32_t f = j < ja.n_joint ? 0u : 2u, b = j < ja.n_joint ? j : j - ja.n_joint;
+      const uint32_t c = joint[f * ja.n_joint + b];
+      if (!c) continue;
+      const unsigned long long cw =
+          a.w0 ? (unsigned long long)c * a.w0 : joint[(f + 1) * ja.n_joint + b];
+      uint64_t* h = f ? ja.fh : ja.jh;
+      atomicAdd((unsigned long long*)&h[2 * (uint64_t)b], (unsigned long long)c);
+      atomicAdd((unsigned long long*)&h[2 * (uint64_t)b + 1], cw);
     }
+    for (uint32_t j = threadIdx.x; j < ntb; j += kAsmNT)
+      if (swd[j] != 0.0) atomicAdd(&ja.wd[j], swd[j]);
   }
 }
 
@@ -579,261 +808,73 @@ __global__ __launch_bounds__(256) void k_sd_prefix(const uint32_t* __restrict__ 
   }
 }
 
-// weight of last occurrences, position order (scanned afterwards)
-__global__ __launch_bounds__(256) void k_sd_lastw(const uint32_t* __restrict__ nxt,
-                                                  const uint8_t* __restrict__ w8, uint64_t n,
-                                                  uint32_t* __restrict__ lw) {
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x)
-    lw[i] = nxt[i] == kNone ? (uint32_t)w8[i] : 0u;
-}
-
-struct SegArgs {
-  uint64_t seg[KV_MAX_GROUPS + 1];
-  uint32_t partitioned;
-};
-
-// Final stack depth of each block = weight of distinct blocks whose last
-// access is at or after its own (inside its segment); bin it.
-template <bool kLds>
-__global__ __launch_bounds__(kAsmNT) void k_sd_finocc(const uint32_t* __restrict__ nxt,
-                                                   const uint8_t* __restrict__ w8,
-                                                   const uint8_t* __restrict__ g8, uint64_t n,
-                                                   const uint32_t* __restrict__ S,
-                                                   SegArgs sa, BinArgs ba) {
-  __shared__ uint32_t sthr[kLds ? kThrLds : 1];
-  __shared__ uint32_t scnt[kLds ? kThrLds + KV_MAX_GROUPS : 1];
-  __shared__ uint32_t sw[kLds ? kThrLds + KV_MAX_GROUPS : 1];
-  __shared__ uint32_t soff[KV_MAX_GROUPS + 1];
-  __shared__ uint32_t send[KV_MAX_GROUPS];
-  const uint32_t nbins = ba.n_thr + ba.n_groups;
-  if (threadIdx.x <= ba.n_groups) soff[threadIdx.x] = ba.off[threadIdx.x];
-  if (threadIdx.x < KV_MAX_GROUPS) {
-    const uint64_t e = sa.partitioned ? sa.seg[threadIdx.x + 1] : n;
-    const uint64_t b = sa.partitioned ? sa.seg[threadIdx.x] : 0;
-    send[threadIdx.x] = (e > b) ? S[e - 1] : 0u;
-  }
-  if (kLds) {
-    for (uint32_t j = threadIdx.x; j < ba.n_thr; j += kAsmNT) sthr[j] = ba.thr[j];
-    for (uint32_t j = threadIdx.x; j < nbins; j += kAsmNT) {
-      scnt[j] = 0;
-      sw[j] = 0;
+// Histograms made cumulative, one workgroup per group and kind (blockIdx.y:
+// 0 the capacity bins, 1 the prefix-reuse ones, 2 the joint ones).
+constexpr uint32_t kCumLds = 8192;  // joint words of one group staged in LDS
+__global__ __launch_bounds__(256) void k_sd_cum(uint64_t* hist, uint64_t* phist,
+                                                const uint32_t* __restrict__ off, JointArgs ja) {
+  __shared__ uint64_t sj[kCumLds];
+  __shared__ double swd[256];
+  const uint32_t g = blockIdx.x, lane = lane_id(), w = (uint32_t)wave_id();
+  const uint32_t nd = off[g + 1] - off[g] + 1;
+  if (blockIdx.y == 1 && !phist) return;
+  if (blockIdx.y < 2) {
+    // a wavefront per field, 64 bins at a time
+    uint64_t* h = (blockIdx.y ? phist : hist) + (uint64_t)(off[g] + g) * 4 + w;
+    uint64_t run = 0;
+    for (uint32_t b = 0; b < nd; b += 64) {
+      const uint32_t i = b + lane;
+      const uint64_t v = wave_incl_scan<uint64_t>(i < nd ? h[(uint64_t)i * 4] : 0ull) + run;
+      if (i < nd) h[(uint64_t)i * 4] = v;
+      run = (uint64_t)__shfl((unsigned long long)v, 63, 64);
     }
+    return;
   }
-  __syncthreads();
-  for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * blockDim.x) {
-    if (nxt[i] != kNone) continue;
-    const uint32_t g = g8[i];
-    const uint32_t w = w8[i];
-    const uint32_t segend = sa.partitioned ? send[g] : send[0];
-    const uint32_t depth = segend - (S[i] - w);
-    const uint32_t lo = soff[g], hi = soff[g + 1];
-    if (kLds) {
-      const uint32_t bin = lo + g + (lower_bound(sthr, lo, hi, depth) - lo);
-      atomicAdd(&scnt[bin], 1u);
-      atomicAdd(&sw[bin], w);
-    } else {
-      const uint32_t bin = lo + g + (lower_bound(ba.thr, lo, hi, depth) - lo);
-      atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 2], 1ull);
-      atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 3], (unsigned long long)w);
-    }
-  }
-  if (kLds) {
+  // both bin dimensions, in LDS where they fit
+  const uint32_t nt = ja.toff[g + 1] - ja.toff[g] + 1, nw = 2 * nd * nt;
+  for (int f = 0; f < 2; ++f) {
+    uint64_t* src = (f ? ja.fh : ja.jh) + 2ull * ja.jbase[g];
+    const bool lds = nw <= kCumLds;
+    uint64_t* h = lds ? sj : src;
+    if (lds)
+      for (uint32_t j = threadIdx.x; j < nw; j += 256) sj[j] = src[j];
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < nbins; j += kAsmNT) {
-      if (scnt[j]) {
-        atomicAdd((unsigned long long*)&ba.hist[j * 4 + 2], (unsigned long long)scnt[j]);
-        atomicAdd((unsigned long long*)&ba.hist[j * 4 + 3], (unsigned long long)sw[j]);
+    for (uint32_t q = threadIdx.x; q < 2 * nd; q += 256) {  // along gap bins
+      uint64_t* x = h + (uint64_t)(q >> 1) * nt * 2 + (q & 1);
+      uint64_t run = 0;
+      for (uint32_t t = 0; t < nt; ++t) {
+        run += x[2 * t];
+        x[2 * t] = run;
       }
     }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Disk TTL tiers.  A bounded TTL tier (capacity C, TTL t, least recently
-// accessed block displaced first) holds a block at access i iff D_i <= C and
-// its gap delta_i <= t: the blocks it holds are the top of the LRU stack up
-// to C, minus those not accessed for t, and with one TTL the latter are a
-// bottom part of the stack (ages grow with depth).  An unbounded one is
-// C = infinity.  So per group one joint histogram of (D bin, gap bin) serves
-// every (capacity, TTL), and one of (final depth bin, end-age bin) gives the
-// blocks held at the last request.
-// ---------------------------------------------------------------------------
-constexpr uint32_t kJointNT = 1024;
-constexpr uint32_t kJThrLds = 2048;     // stack-distance thresholds in LDS
-constexpr uint32_t kJTtlLds = 1024;     // TTL values (+ groups) in LDS
-constexpr uint32_t kJBinsLds = 4096;    // joint bins in LDS
-
-struct JointLds {
-  uint32_t thr[kJThrLds];
-  double tthr[kJTtlLds];
-  double wd[kJTtlLds];
-  uint32_t jc[kJBinsLds], jw[kJBinsLds];
-  uint32_t off[KV_MAX_GROUPS + 1], toff[KV_MAX_GROUPS + 1], jbase[KV_MAX_GROUPS + 1];
-};
-
-template <bool kLds>
-__device__ __forceinline__ void joint_setup(JointLds& L, const BinArgs& ba, const JointArgs& ja) {
-  const uint32_t G = ba.n_groups;
-  if (threadIdx.x <= G) {
-    L.off[threadIdx.x] = ba.off[threadIdx.x];
-    L.toff[threadIdx.x] = ja.toff[threadIdx.x];
-    L.jbase[threadIdx.x] = ja.jbase[threadIdx.x];
-  }
-  if (kLds) {
-    for (uint32_t j = threadIdx.x; j < ba.n_thr; j += kJointNT) L.thr[j] = ba.thr[j];
-    for (uint32_t j = threadIdx.x; j < ja.n_tthr; j += kJointNT) L.tthr[j] = ja.tthr[j];
-    for (uint32_t j = threadIdx.x; j < ja.n_tthr + G; j += kJointNT) L.wd[j] = 0.0;
-    for (uint32_t j = threadIdx.x; j < ja.n_joint; j += kJointNT) L.jc[j] = L.jw[j] = 0;
-  }
-  __syncthreads();
-}
-
-// bin of (d, x) in group g: d against the capacities, x against the TTLs
-template <bool kLds>
-__device__ __forceinline__ uint32_t joint_bin(const JointLds& L, const BinArgs& ba,
-                                              const JointArgs& ja, uint32_t g, uint32_t d,
-                                              bool has_x, double x, uint32_t* tb) {
-  const uint32_t lo = L.off[g], hi = L.off[g + 1];
-  const uint32_t db = d == kNone ? hi - lo
-                                 : (kLds ? lower_bound(L.thr, lo, hi, d) : lower_bound(ba.thr, lo, hi, d)) - lo;
-  const uint32_t tlo = L.toff[g], thi = L.toff[g + 1];
-  const uint32_t t = !has_x ? thi - tlo
-                            : (kLds ? lower_bound(L.tthr, tlo, thi, x) : lower_bound(ja.tthr, tlo, thi, x)) - tlo;
-  *tb = tlo + g + t;
-  return L.jbase[g] + db * (thi - tlo + 1) + t;
-}
-
-template <bool kLds>
-__device__ __forceinline__ void joint_flush(JointLds& L, const JointArgs& ja, uint64_t* h,
-                                            uint32_t n_groups, bool with_wd) {
-  if (!kLds) return;
-  __syncthreads();
-  for (uint32_t j = threadIdx.x; j < ja.n_joint; j += kJointNT) {
-    if (L.jc[j]) {
-      atomicAdd((unsigned long long*)&h[2 * (uint64_t)j], (unsigned long long)L.jc[j]);
-      atomicAdd((unsigned long long*)&h[2 * (uint64_t)j + 1], (unsigned long long)L.jw[j]);
+    __syncthreads();
+    for (uint32_t q = threadIdx.x; q < 2 * nt; q += 256) {  // along distance bins
+      uint64_t run = 0;
+      for (uint32_t d = 0; d < nd; ++d) {
+        uint64_t& x = h[(uint64_t)d * nt * 2 + q];
+        run += x;
+        x = run;
+      }
     }
+    __syncthreads();
+    if (lds)
+      for (uint32_t j = threadIdx.x; j < nw; j += 256) src[j] = sj[j];
+    __syncthreads();
   }
-  if (with_wd)
-    for (uint32_t j = threadIdx.x; j < ja.n_tthr + n_groups; j += kJointNT)
-      if (L.wd[j] != 0.0) atomicAdd(&ja.wd[j], L.wd[j]);
-}
-
-// Accesses by (stack distance, gap to the block's previous access), plus the
-// weighted gaps per gap bin (for the storage integral).
-template <bool kLds>
-__global__ __launch_bounds__(kJointNT) void k_sd_joint(const uint32_t* __restrict__ dist,
-                                                       const uint32_t* __restrict__ key,
-                                                       const uint32_t* __restrict__ req,
-                                                       const double* __restrict__ rt,
-                                                       const uint8_t* __restrict__ w8,
-                                                       const uint8_t* __restrict__ g8, uint64_t n,
-                                                       BinArgs ba, JointArgs ja) {
-  __shared__ JointLds L;
-  joint_setup<kLds>(L, ba, ja);
-  for (uint64_t i = (uint64_t)blockIdx.x * kJointNT + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * kJointNT) {
-    const uint32_t k = key[i];
-    const uint32_t g = g8[i], w = w8[i];
-    const double gap = k ? rt[req[i]] - rt[req[k - 1]] : 0.0;
-    uint32_t tb;
-    const uint32_t b = joint_bin<kLds>(L, ba, ja, g, dist[i], k != 0, gap, &tb);
-    if (kLds) {
-      atomicAdd(&L.jc[b], 1u);
-      atomicAdd(&L.jw[b], w);
-      if (k) atomicAdd(&L.wd[tb], (double)w * gap);
-    } else {
-      atomicAdd((unsigned long long*)&ja.jh[2 * (uint64_t)b], 1ull);
-      atomicAdd((unsigned long long*)&ja.jh[2 * (uint64_t)b + 1], (unsigned long long)w);
-      if (k) atomicAdd(&ja.wd[tb], (double)w * gap);
-    }
-  }
-  joint_flush<kLds>(L, ja, ja.jh, ba.n_groups, true);
-}
-
-// Blocks by (final stack depth, age at the last request), at their last access.
-template <bool kLds>
-__global__ __launch_bounds__(kJointNT) void k_sd_finjoint(const uint32_t* __restrict__ nxt,
-                                                          const uint32_t* __restrict__ req,
-                                                          const double* __restrict__ rt,
-                                                          const uint8_t* __restrict__ w8,
-                                                          const uint8_t* __restrict__ g8,
-                                                          uint64_t n,
-                                                          const uint32_t* __restrict__ S,
-                                                          BinArgs ba, JointArgs ja) {
-  __shared__ JointLds L;
-  joint_setup<kLds>(L, ba, ja);
-  const uint32_t segend = S[n - 1];
-  const double t_end = rt[req[n - 1]];  // the last access's request
-  for (uint64_t i = (uint64_t)blockIdx.x * kJointNT + threadIdx.x; i < n;
-       i += (uint64_t)gridDim.x * kJointNT) {
-    if (nxt[i] != kNone) continue;
-    const uint32_t g = g8[i], w = w8[i];
-    const uint32_t depth = segend - (S[i] - w);
-    uint32_t tb;
-    const uint32_t b = joint_bin<kLds>(L, ba, ja, g, depth, true, t_end - rt[req[i]], &tb);
-    if (kLds) {
-      atomicAdd(&L.jc[b], 1u);
-      atomicAdd(&L.jw[b], w);
-    } else {
-      atomicAdd((unsigned long long*)&ja.fh[2 * (uint64_t)b], 1ull);
-      atomicAdd((unsigned long long*)&ja.fh[2 * (uint64_t)b + 1], (unsigned long long)w);
-    }
-  }
-  joint_flush<kLds>(L, ja, ja.fh, ba.n_groups, false);
-}
-
-// Cumulative over both bin dimensions, one block per group; wd over gap bins.
-__global__ __launch_bounds__(256) void k_joint_cum(uint64_t* __restrict__ jh,
-                                                   uint64_t* __restrict__ fh,
-                                                   double* __restrict__ wd,
-                                                   const uint32_t* __restrict__ off,
-                                                   const uint32_t* __restrict__ toff,
-                                                   const uint32_t* __restrict__ jbase) {
-  const uint32_t g = blockIdx.x;
-  const uint32_t nd = off[g + 1] - off[g] + 1, nt = toff[g + 1] - toff[g] + 1;
-  const uint64_t b0 = jbase[g];
-  for (uint32_t q = threadIdx.x; q < 4 * nd; q += blockDim.x) {  // along gap bins
-    uint64_t* h = (q & 2) ? fh : jh;
-    const uint32_t f = q & 1, d = q >> 2;
-    uint64_t run = 0;
-    for (uint32_t t = 0; t < nt; ++t) {
-      uint64_t& x = h[2 * (b0 + (uint64_t)d * nt + t) + f];
-      run += x;
-      x = run;
-    }
-  }
-  __syncthreads();
-  for (uint32_t q = threadIdx.x; q < 4 * nt; q += blockDim.x) {  // along distance bins
-    uint64_t* h = (q & 2) ? fh : jh;
-    const uint32_t f = q & 1, t = q >> 2;
-    uint64_t run = 0;
-    for (uint32_t d = 0; d < nd; ++d) {
-      uint64_t& x = h[2 * (b0 + (uint64_t)d * nt + t) + f];
-      run += x;
-      x = run;
-    }
-  }
-  if (threadIdx.x == 0) {
-    double run = 0.0;
-    for (uint32_t t = 0; t < nt; ++t) {
-      run += wd[toff[g] + g + t];
-      wd[toff[g] + g + t] = run;
-    }
-  }
-}
-
-// cumulative over the bins of each group, one thread per (group, field)
-__global__ void k_hist_cum(uint64_t* hist, const uint32_t* __restrict__ off, uint32_t n_groups) {
-  const uint32_t g = threadIdx.x / 4, f = threadIdx.x % 4;
-  if (g >= n_groups) return;
-  const uint32_t b0 = off[g] + g, b1 = off[g + 1] + g + 1;
-  uint64_t run = 0;
-  for (uint32_t b = b0; b < b1; ++b) {
-    run += hist[b * 4 + f];
-    hist[b * 4 + f] = run;
+  double run = 0.0;  // weighted gaps over gap bins
+  double* wd = ja.wd + ja.toff[g] + g;
+  for (uint32_t b = 0; b < nt; b += 256) {
+    const uint32_t m = min(256u, nt - b);
+    if (threadIdx.x < m) swd[threadIdx.x] = wd[b + threadIdx.x];
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (uint32_t t = 0; t < m; ++t) {
+        run += swd[t];
+        swd[t] = run;
+      }
+    __syncthreads();
+    if (threadIdx.x < m) wd[b + threadIdx.x] = swd[threadIdx.x];
+    __syncthreads();
   }
 }
 
@@ -859,8 +900,8 @@ uint32_t grid_of(uint64_t m, uint32_t cap = 32768) {
 // log2 of the position block.  Small blocks sort in fewer merge levels, and
 // more of them fit a compute unit and run at once; the block matrix grows
 // with the square of their number.  Matrix and in-block kernels, us, for
-// blocks of 1,024 / 2,048 / 4,096 / 8,192: 238,313 accesses 68 / 67 / 70 / 87;
-// 4.6e6: 214 / 181 / 189 / 228; 1.09e8: 24,780 / 8,740 / 4,380 / 3,560.
+// blocks of 1,024 / 2,048 / 4,096 / 8,192: 238,313 accesses 43 / 47 / 57 / 84;
+// 4.6e6: 216 / 173 / 171 / 246; 1.09e8: 46,230 / 11,080 / 4,950 / 3,730.
 uint32_t block_log(uint64_t n) {
   if (const char* e = std::getenv("KVCFG_TEST_BLOCK_LOG"))
     return (uint32_t)std::min(13ul, std::max(10ul, std::strtoul(e, nullptr, 10)));
@@ -878,27 +919,21 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
   const bool uni = t.st.w_min == t.st.w_max;
   kv_status st;
   const uint64_t tri = G >= 2 ? tri_off(G) : 1;
-  const uint32_t nchunks = div_up(G, kColRows);
   DevBuf& b_partial = t.ws[0];
   DevBuf& b_E = t.ws[1];
   DevBuf& b_Q = t.ws[2];
-  DevBuf& b_csum = t.ws[3];
-  DevBuf& b_scan = t.ws[4];
+  DevBuf& b_last = t.ws[3];  // per part of a block: weight of its last occurrences, and before
   if ((st = b_partial.reserve(n * 4)) != KV_OK) return st;
   if ((st = b_E.reserve(n * 4)) != KV_OK) return st;
   if ((st = b_Q.reserve(tri * 4)) != KV_OK) return st;
-  if ((st = b_csum.reserve((uint64_t)nchunks * G * 4)) != KV_OK) return st;
-  if ((st = b_scan.reserve(std::max<uint64_t>(scan_scratch_elems(n), 1) * 4)) != KV_OK) return st;
-  // prefix reuse and disk TTL tiers (trace order only): every access's
-  // distance; request starts
+  if ((st = b_last.reserve((2ull * kSubs * G + KV_MAX_GROUPS) * 4)) != KV_OK) return st;
+  if ((phist || ja) && partitioned) return fail(KV_ERR_UNSUPPORTED, "this mode needs the trace order");
+  // prefix reuse: every access's distance; request starts
   uint32_t* dist = nullptr;
   uint32_t* rstart = nullptr;
-  if (phist || ja) {
-    if (partitioned) return fail(KV_ERR_UNSUPPORTED, "this mode needs the trace order");
+  if (phist) {
     if ((st = t.ws[25].reserve(n * 4)) != KV_OK) return st;
     dist = t.ws[25].as<uint32_t>();
-  }
-  if (phist) {
     if ((st = t.ws[26].reserve(((uint64_t)t.st.n_req + 1) * 4)) != KV_OK) return st;
     rstart = t.ws[26].as<uint32_t>();
   }
@@ -907,19 +942,34 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
   const uint8_t* w8 = o.w.as<uint8_t>();
   const uint8_t* g8 = o.g.as<uint8_t>();
   uint32_t* Q = b_Q.as<uint32_t>();
-  if (G >= 2) {
+  uint32_t* lsum = b_last.as<uint32_t>();
+  uint32_t* lpre = lsum + G * kSubs;
+  uint32_t* segend = lpre + G * kSubs;
+  SegArgs sa{};
+  for (int g = 0; g <= KV_MAX_GROUPS; ++g) sa.seg[g] = o.seg[g];
+  sa.partitioned = partitioned ? 1u : 0u;
+  {
     StageTimer tm(kStStackMatrix, s);
     const uint32_t row_chunk = env_limit("KVCFG_TEST_ROW_CHUNK", kRowChunk, 1);
-    hipLaunchKernelGGL(k_sd_rowhist, dim3(G), dim3(kRowNT), 0, s, key, w8, n, logb, row_chunk, Q);
+    Zero z{};
+    z.p[0] = hist;
+    z.n[0] = ts.total_bins() * 4;
+    z.p[1] = phist;
+    z.n[1] = phist ? ts.total_bins() * 4 : 0;
+    z.p[2] = ja ? ja->jh : nullptr;  // jh, fh and wd lie together
+    z.n[2] = ja ? 4 * ja->n_joint + ja->n_tthr + ts.n_groups : 0;
+    hipLaunchKernelGGL(k_sd_rowhist, dim3(G), dim3(kRowNT), 0, s, key, nxt, w8,
+                       uni ? t.st.w_max : 0u, n, logb, row_chunk,
+                       Q, lsum, z);
     KV_HIP(hipGetLastError());
-    const dim3 cg(div_up(G, 256), nchunks);
-    hipLaunchKernelGGL(k_sd_colsum, cg, dim3(256), 0, s, Q, G, b_csum.as<uint32_t>());
-    KV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sd_colchunks, dim3(div_up(G, 256)), dim3(256), 0, s,
-                       b_csum.as<uint32_t>(), G, nchunks);
-    KV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_sd_colapply, cg, dim3(256), 0, s, Q, G,
-                       (const uint32_t*)b_csum.as<uint32_t>());
+    // 16 columns per workgroup, more of them, for a few thousand blocks; 32
+    // (whole cache lines) where the matrix does not stay in the caches
+    const auto cols = [&](auto kernel, uint32_t c) {
+      hipLaunchKernelGGL(kernel, dim3(div_up(G - 1, c) + 1), dim3(kRowNT), 0, s, Q, G, lsum, lpre,
+                         segend, nxt, w8, n, logb, sa);
+    };
+    if (G <= 4096) cols(k_sd_cols<16>, 16);
+    else cols(k_sd_cols<32>, 32);
     KV_HIP(hipGetLastError());
   }
   {
@@ -939,87 +989,59 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
   BinArgs ba{thr_dev, off_dev, (uint32_t)ts.values.size(), ts.n_groups, hist};
   const uint32_t lds_limit = env_limit("KVCFG_TEST_THR_LDS", kThrLds, 0);
   const bool lds = ts.values.size() + ts.n_groups <= lds_limit;
-  const bool jlds = ja && lds_limit > 0 && ts.values.size() <= kJThrLds &&
-                    ja->n_tthr + ts.n_groups <= kJTtlLds && ja->n_joint <= kJBinsLds;
-  const uint32_t gj = std::min<uint32_t>(div_up(n, kJointNT), 1024);
-  // two workgroups per compute unit (their LDS histograms allow two): each
-  // flushes its histogram once, so fewer and larger ones flush less
-  const uint32_t ga = std::min<uint32_t>(G, 512);
+  uint64_t bytes = lds ? (ts.values.size() + 4ull * ts.total_bins()) * 4 : 0;
+  const uint64_t jbytes = ja ? (2ull * ja->n_tthr + ts.n_groups) * 8 + 16ull * ja->n_joint : 0;
+  const bool jlds = ja && lds && lds_limit > 0 && bytes + jbytes <= kAsmLds;
+  if (jlds) bytes += jbytes;
   {
-  StageTimer tm(kStStackAssemble, s);
-  if (lds)
-    hipLaunchKernelGGL(k_sd_assemble<true>, dim3(ga), dim3(kAsmNT), 0, s, key, w8, g8, n, logb, G,
-                       (const uint32_t*)b_partial.as<uint32_t>(),
-                       (const uint32_t*)b_E.as<uint32_t>(), (const uint32_t*)Q, ba, dist, real);
-  else
-    hipLaunchKernelGGL(k_sd_assemble<false>, dim3(ga), dim3(kAsmNT), 0, s, key, w8, g8, n, logb, G,
-                       (const uint32_t*)b_partial.as<uint32_t>(),
-                       (const uint32_t*)b_E.as<uint32_t>(), (const uint32_t*)Q, ba, dist, real);
-  KV_HIP(hipGetLastError());
-  if (phist) {
-    const uint32_t nr = t.st.n_req;
-    hipLaunchKernelGGL(k_sd_rstart, dim3(grid_of(n + 1)), dim3(256), 0, s,
-                       t.req.as<uint32_t>(), n, nr, rstart);
+    StageTimer tm(kStStackAssemble, s);
+    AsmArgs aa{key, nxt, w8, g8, real, n, uni ? t.st.w_max : 0u, logb, G,
+               b_partial.as<uint32_t>(), b_E.as<uint32_t>(), Q, dist, lpre, segend,
+               sa.partitioned, t.req.as<uint32_t>(), t.req_time.as<double>()};
+    // two workgroups per compute unit where their LDS allows: each flushes
+    // its histograms once, so fewer and larger ones flush less
+    const uint32_t ga = std::min<uint32_t>(G, 512);
+    const JointArgs none{};
+    const auto assemble = [&](auto kernel) {
+      if (bytes > 64 * 1024 &&  // has to be asked for
+          hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+        (void)hipGetLastError();
+      hipLaunchKernelGGL(kernel, dim3(ga), dim3(kAsmNT), (uint32_t)bytes, s, aa, ba, ja ? *ja : none);
+    };
+    const auto by_rows = [&](auto r) {
+      constexpr int R = decltype(r)::value;
+      if (jlds) assemble(k_sd_assemble<R, true, 1>);
+      else if (ja) lds ? assemble(k_sd_assemble<R, true, 2>) : assemble(k_sd_assemble<R, false, 2>);
+      else lds ? assemble(k_sd_assemble<R, true, 0>) : assemble(k_sd_assemble<R, false, 0>);
+    };
+    switch (logb) {
+      case 10: by_rows(std::integral_constant<int, 1>{}); break;
+      case 11: by_rows(std::integral_constant<int, 2>{}); break;
+      case 12: by_rows(std::integral_constant<int, 4>{}); break;
+      default: by_rows(std::integral_constant<int, 8>{});
+    }
     KV_HIP(hipGetLastError());
-    BinArgs bp{thr_dev, off_dev, (uint32_t)ts.values.size(), ts.n_groups, phist};
-    const uint32_t gp = std::min<uint32_t>(div_up(nr, 4), 4096);
-    if (lds)
-      hipLaunchKernelGGL(k_sd_prefix<true>, dim3(gp), dim3(256), 0, s, (const uint32_t*)dist,
-                         (const uint32_t*)rstart, nr, w8, g8, bp);
-    else
-      hipLaunchKernelGGL(k_sd_prefix<false>, dim3(gp), dim3(256), 0, s, (const uint32_t*)dist,
-                         (const uint32_t*)rstart, nr, w8, g8, bp);
-    KV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_hist_cum, dim3(1), dim3(4 * KV_MAX_GROUPS), 0, s, phist, off_dev,
-                       ts.n_groups);
-    KV_HIP(hipGetLastError());
-  }
-  if (ja) {
-    const uint32_t* rq = t.req.as<uint32_t>();
-    const double* rt = t.req_time.as<double>();
-    if (jlds)
-      hipLaunchKernelGGL(k_sd_joint<true>, dim3(gj), dim3(kJointNT), 0, s, (const uint32_t*)dist,
-                         key, rq, rt, w8, g8, n, ba, *ja);
-    else
-      hipLaunchKernelGGL(k_sd_joint<false>, dim3(gj), dim3(kJointNT), 0, s,
-                         (const uint32_t*)dist, key, rq, rt, w8, g8, n, ba, *ja);
-    KV_HIP(hipGetLastError());
-  }
+    if (phist) {
+      const uint32_t nr = t.st.n_req;
+      hipLaunchKernelGGL(k_sd_rstart, dim3(grid_of(n + 1)), dim3(256), 0, s,
+                         t.req.as<uint32_t>(), n, nr, rstart);
+      KV_HIP(hipGetLastError());
+      BinArgs bp{thr_dev, off_dev, (uint32_t)ts.values.size(), ts.n_groups, phist};
+      const uint32_t gp = std::min<uint32_t>(div_up(nr, 4), 4096);
+      if (lds)
+        hipLaunchKernelGGL(k_sd_prefix<true>, dim3(gp), dim3(256), 0, s, (const uint32_t*)dist,
+                           (const uint32_t*)rstart, nr, w8, g8, bp);
+      else
+        hipLaunchKernelGGL(k_sd_prefix<false>, dim3(gp), dim3(256), 0, s, (const uint32_t*)dist,
+                           (const uint32_t*)rstart, nr, w8, g8, bp);
+      KV_HIP(hipGetLastError());
+    }
   }
   StageTimer tm(kStStackFinal, s);
-  // final occupancy: reuse `partial` for the scanned last-occurrence weights
-  uint32_t* S = b_partial.as<uint32_t>();
-  hipLaunchKernelGGL(k_sd_lastw, dim3(grid_of(n)), dim3(256), 0, s, nxt, w8, n, S);
+  hipLaunchKernelGGL(k_sd_cum, dim3(ts.n_groups, ja ? 3 : phist ? 2 : 1), dim3(256), 0, s, hist,
+                     phist, off_dev, ja ? *ja : JointArgs{});
   KV_HIP(hipGetLastError());
-  if ((st = scan_u32(S, S, n, true, b_scan.as<uint32_t>(), s)) != KV_OK) return st;
-  SegArgs sa{};
-  for (int g = 0; g <= KV_MAX_GROUPS; ++g) sa.seg[g] = o.seg[g];
-  sa.partitioned = partitioned ? 1u : 0u;
-  const uint32_t gf = std::min<uint32_t>(div_up(n, kAsmNT), 512);  // two per compute unit, as above
-  if (lds)
-    hipLaunchKernelGGL(k_sd_finocc<true>, dim3(gf), dim3(kAsmNT), 0, s, nxt, w8, g8, n,
-                       (const uint32_t*)S, sa, ba);
-  else
-    hipLaunchKernelGGL(k_sd_finocc<false>, dim3(gf), dim3(kAsmNT), 0, s, nxt, w8, g8, n,
-                       (const uint32_t*)S, sa, ba);
-  KV_HIP(hipGetLastError());
-  hipLaunchKernelGGL(k_hist_cum, dim3(1), dim3(4 * KV_MAX_GROUPS), 0, s, hist, off_dev,
-                     ts.n_groups);
-  KV_HIP(hipGetLastError());
-  if (ja) {
-    const uint32_t* rq = t.req.as<uint32_t>();
-    const double* rt = t.req_time.as<double>();
-    if (jlds)
-      hipLaunchKernelGGL(k_sd_finjoint<true>, dim3(gj), dim3(kJointNT), 0, s, nxt, rq, rt, w8,
-                         g8, n, (const uint32_t*)S, ba, *ja);
-    else
-      hipLaunchKernelGGL(k_sd_finjoint<false>, dim3(gj), dim3(kJointNT), 0, s, nxt, rq, rt, w8,
-                         g8, n, (const uint32_t*)S, ba, *ja);
-    KV_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_joint_cum, dim3(ts.n_groups), dim3(256), 0, s, ja->jh, ja->fh, ja->wd,
-                       off_dev, ja->toff, ja->jbase);
-    KV_HIP(hipGetLastError());
-  }
   return KV_OK;
 }
 

@@ -352,7 +352,7 @@ void finish_set(ThresholdSet& ts, std::vector<std::vector<uint32_t>>& per_group,
 
 // The disk TTL tiers' bins: per group its sorted distinct TTL values, the
 // joint histograms' layout (bins of group g: (capacities + 1) x (TTLs + 1)),
-// zeroed device histograms.  Needs the shared threshold set built.
+// the histograms' memory.  Needs the shared threshold set built.
 kv_status plan_joint(Trace& t, std::vector<std::vector<double>>& per_group, JointArgs& ja,
                      JointView& jv, hipStream_t s) {
   const uint32_t G = t.n_groups;
@@ -390,7 +390,6 @@ kv_status plan_joint(Trace& t, std::vector<std::vector<double>>& per_group, Join
   if ((st = bh.reserve(hwords * 8)) != KV_OK) return st;
   KV_HIP(hipMemcpyAsync(bt.p, t.joint_stage.data(), t.joint_stage.size() * 4,
                         hipMemcpyHostToDevice, s));
-  if ((st = fill_u64(bh.as<uint64_t>(), 0, hwords, s)) != KV_OK) return st;
   ja.tthr = bt.as<double>();
   ja.toff = bt.as<uint32_t>() + 2 * nt;
   ja.jbase = ja.toff + G + 1;
@@ -426,12 +425,10 @@ kv_status run_stack(Trace& t, Order& o, bool partitioned, ThresholdSet& ts, Stac
   uint32_t* off = thr + nthr;
   if (nthr) KV_HIP(hipMemcpyAsync(thr, ts.values.data(), nthr * 4, hipMemcpyHostToDevice, s));
   KV_HIP(hipMemcpyAsync(off, ts.off, (KV_MAX_GROUPS + 1) * 4, hipMemcpyHostToDevice, s));
-  if ((st = fill_u64(bh.as<uint64_t>(), 0, nbins * 4, s)) != KV_OK) return st;
   uint64_t* ph = nullptr;
   if (slot.ws_phist >= 0) {
     DevBuf& bp = t.ws[slot.ws_phist];
     if ((st = bp.reserve(nbins * 4 * 8)) != KV_OK) return st;
-    if ((st = fill_u64(bp.as<uint64_t>(), 0, nbins * 4, s)) != KV_OK) return st;
     ph = bp.as<uint64_t>();
   }
   if ((st = stack_pass(t, o, partitioned, ts, thr, off, bh.as<uint64_t>(), ph, ja, real, s)) !=

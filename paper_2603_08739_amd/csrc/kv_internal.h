@@ -96,9 +96,9 @@ struct JointArgs {
   const uint32_t* toff = nullptr;  // [G + 1], device
   const uint32_t* jbase = nullptr; // [G + 1], device
   uint32_t n_tthr = 0, n_joint = 0;
-  uint64_t* jh = nullptr;          // [n_joint][2] count, weight (zeroed)
-  uint64_t* fh = nullptr;          // [n_joint][2] count, weight (zeroed)
-  double* wd = nullptr;            // [n_tthr + G] sum of w * gap per (group, gap bin) (zeroed)
+  uint64_t* jh = nullptr;          // [n_joint][2] count, weight
+  uint64_t* fh = nullptr;          // [n_joint][2] count, weight; follows jh
+  double* wd = nullptr;            // [n_tthr + G] sum of w * gap per (group, gap bin); follows fh
 };
 
 struct Trace {
@@ -187,8 +187,8 @@ kv_status leaf_prepare(Trace& t, hipStream_t s);
 // stack-distance pass (k_stack.hip)
 // hist: u64[total_bins][4] = {count, weight, final count, final weight},
 // made cumulative over the bins of each group on return.
-// thr_dev / off_dev: device copies of ts.values / ts.off; hist must be zeroed.
-// phist (zeroed, same layout, or NULL; trace order only): fields 0 and 1
+// thr_dev / off_dev: device copies of ts.values / ts.off.
+// phist (same layout, or NULL; trace order only): fields 0 and 1
 // count the accesses by their request-prefix distance (prefix reuse).
 // ja (or NULL; trace order only): the joint histograms of disk TTL tiers,
 // made cumulative over both bin dimensions (and wd over gap bins) on return.
