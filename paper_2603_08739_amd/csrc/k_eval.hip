@@ -96,7 +96,7 @@ __device__ __forceinline__ void ttl_tier_record(const OrderView& ov, const Joint
 // at its own capacity and at the largest faster one (the sum of the faster
 // ones in the exclusive mode).  Bound by the chain of a threshold search, so
 // a tier has a thread of its own (one thread for all three, each field
-// searched for by itself: 13 us for 25 configurations, 22 us for 527; now 7
+// searched for by itself: 13 us for 25 configurations, 22 us for 527; now 9
 // and 11 us).
 __global__ __launch_bounds__(256) void k_lru_counts(const kv_config* __restrict__ cfg,
                                                     uint32_t n_cfg, uint32_t G, OrderView sh,
