@@ -192,9 +192,10 @@ __global__ __launch_bounds__(kRsNT) void k_load_tiles(
   }
 }
 
-__global__ void k_load_init(DevStats* st) {
+__global__ void k_load_init(DevStats* st, uint32_t* err) {
   uint32_t* p = reinterpret_cast<uint32_t*>(st);
   for (uint32_t i = threadIdx.x; i < sizeof(DevStats) / 4; i += blockDim.x) p[i] = 0;
+  if (threadIdx.x < 2) err[threadIdx.x] = 0;  // the replays' error record
   __syncthreads();
   if (threadIdx.x == 0) st->w_min = 0xFFFFFFFFu;
 }
@@ -1035,7 +1036,8 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
   uint32_t* cnt = counts.as<uint32_t>();
   {
     StageTimer tm(kStLoadValidate, s);
-    hipLaunchKernelGGL(k_load_init, dim3(1), dim3(64), 0, s, dstats);
+    hipLaunchKernelGGL(k_load_init, dim3(1), dim3(64), 0, s, dstats,
+                       t.err.as<uint32_t>());
     KV_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_load_tiles, dim3(std::min<uint32_t>(ntiles, kReduceGrid)), dim3(kRsNT), 0,
                        s, d.hash, d.req, d.group, d.weight, n, d.req_time, d.n_req, d.n_groups,
@@ -1105,14 +1107,16 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
                        t.blk_w.as<uint8_t>(), t.blk_g.as<uint8_t>(), dstats);
     KV_HIP(hipGetLastError());
   }
-  DevStats hs;
-  KV_HIP(hipMemcpyAsync(&hs, dstats, sizeof(DevStats), hipMemcpyDeviceToHost, s));
+  // the statistics come back through the handle's pinned block
+  static_assert(sizeof(DevStats) % 16 == 0 && sizeof(DevStats) + 256 <= 4096, "copied in words of 16");
+  DevStats& hs = *reinterpret_cast<DevStats*>(t.err_pin->host + 256);
+  if ((st = copy_words(dstats, t.err_pin->dev + 256, sizeof(DevStats), s)) != KV_OK) return st;
   KV_HIP(hipStreamSynchronize(s));
   if (sorted || hs.full) {
     // (nothing of the blocks was counted or checked when a table was full)
     for (DevBuf* b : {&ka, &kb, &va, &vb, &d1, &d2}) b->release();
     if ((st = canon_sorted(t, d, dstats, counts, scratch, s)) != KV_OK) return st;
-    KV_HIP(hipMemcpyAsync(&hs, dstats, sizeof(DevStats), hipMemcpyDeviceToHost, s));
+    if ((st = copy_words(dstats, t.err_pin->dev + 256, sizeof(DevStats), s)) != KV_OK) return st;
     KV_HIP(hipStreamSynchronize(s));
   }
   if (hs.err) {

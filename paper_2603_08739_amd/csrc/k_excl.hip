@@ -861,7 +861,7 @@ kv_status excl_run(Trace& t, const kv_config* cfg_host, uint32_t n_cfg, const Gr
   if (w0 == 0 && (st = walk_range(0, n_lru + 1)) != KV_OK) return st;
   // a failed state check is reported by the next call on this trace
   KV_HIP(hipMemcpyAsync(t.err_host, t.err.p, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-  KV_HIP(hipEventRecord(t.err_ev, s));
+  KV_HIP(hipEventRecord(t.err_pin->ev, s));
   t.err_pending = true;
   return KV_OK;
 }

@@ -2773,7 +2773,7 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
     for (size_t i = 0; i < jd.size(); ++i)
       t.err_jobs[i] = ReplayJobInfo{jd[i].policy, jd[i].group, jd[i].cap};
     KV_HIP(hipMemcpyAsync(t.err_host, t.err.p, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
-    KV_HIP(hipEventRecord(t.err_ev, s));
+    KV_HIP(hipEventRecord(t.err_pin->ev, s));
     t.err_pending = true;
   }
   return KV_OK;

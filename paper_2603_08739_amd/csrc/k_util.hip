@@ -1,4 +1,6 @@
 // k_util.hip - device-wide prefix sums and fills.
+#include <algorithm>
+
 #include "kv_device.h"
 #include "kv_internal.h"
 
@@ -68,6 +70,12 @@ __global__ void k_fill_u64(uint64_t* p, uint64_t v, uint64_t m) {
     p[i] = v;
 }
 
+__global__ __launch_bounds__(256) void k_copy(const uint4* __restrict__ src, uint4* __restrict__ dst,
+                                              uint64_t m) {
+  for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < m; i += (uint64_t)gridDim.x * 256)
+    dst[i] = src[i];
+}
+
 uint32_t grid_for(uint64_t m, uint32_t nt) {
   uint64_t g = (m + nt - 1) / nt;
   if (g > 65536) g = 65536;
@@ -86,6 +94,15 @@ kv_status fill_u32(uint32_t* p, uint32_t v, uint64_t m, hipStream_t s) {
 kv_status fill_u64(uint64_t* p, uint64_t v, uint64_t m, hipStream_t s) {
   if (m == 0) return KV_OK;
   hipLaunchKernelGGL(k_fill_u64, dim3(grid_for(m, 256)), dim3(256), 0, s, p, v, m);
+  KV_HIP(hipGetLastError());
+  return KV_OK;
+}
+
+kv_status copy_words(const void* src, void* dst, uint64_t bytes, hipStream_t s) {
+  const uint64_t m = bytes / 16;
+  if (m == 0) return KV_OK;
+  hipLaunchKernelGGL(k_copy, dim3((uint32_t)std::min<uint64_t>((m + 255) / 256, 1024)), dim3(256), 0,
+                     s, (const uint4*)src, (uint4*)dst, m);
   KV_HIP(hipGetLastError());
   return KV_OK;
 }

@@ -193,17 +193,94 @@ void DevBuf::release() {
   bytes = 0;
 }
 
+// Pinned host blocks, kept per device and handed out again: pinning memory
+// and creating an event for every trace, and freeing them, took 100 us (a
+// small trace's load 186 -> 127 us, its free 45 -> 3 us).
+// A block goes back with its event recorded behind the last device work that
+// reads or writes it, and is handed out once that is done, so it can serve
+// any thread and stream.  At most kPinKeep bytes are kept per device.
+namespace {
+constexpr size_t kPinKeep = 8u << 20;
+std::mutex g_pin_mu;
+std::vector<PinBlock*> g_pins[64];  // given back; device work may still use them
+size_t g_pin_bytes[64] = {};        // of the blocks above
+
+// Event queries and pinned allocations would end a graph capture that some
+// other thread has under way.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+}  // namespace
+
+kv_status pin_take(size_t bytes, PinBlock** out) {
+  *out = nullptr;
+  int d = 0;
+  KV_HIP(hipGetDevice(&d));
+  if (d < 0 || d >= 64) return fail(KV_ERR_DEVICE, "device index out of range");
+  size_t sz = 4096;
+  while (sz < bytes) sz *= 2;
+  RelaxedCapture relaxed;
+  {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    auto& v = g_pins[d];
+    for (size_t i = 0; i < v.size(); ++i) {
+      if (v[i]->bytes != sz) continue;
+      const hipError_t q = hipEventQuery(v[i]->ev);
+      if (q == hipErrorNotReady) continue;
+      if (q != hipSuccess) {
+        (void)hipGetLastError();
+        continue;
+      }
+      *out = v[i];
+      g_pin_bytes[d] -= sz;
+      v.erase(v.begin() + i);
+      return KV_OK;
+    }
+  }
+  auto* b = new PinBlock();
+  b->bytes = sz;
+  b->device = d;
+  hipError_t e = hipHostMalloc((void**)&b->host, sz, hipHostMallocDefault);
+  if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&b->dev, b->host, 0);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&b->ev, hipEventDisableTiming);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (b->host) (void)hipHostFree(b->host);
+    delete b;
+    return hip_fail(e, "pinned host memory");
+  }
+  *out = b;
+  return KV_OK;
+}
+
+void pin_give(PinBlock* b) {
+  {
+    std::lock_guard<std::mutex> lk(g_pin_mu);
+    if (g_pin_bytes[b->device] + b->bytes <= kPinKeep) {
+      g_pins[b->device].push_back(b);
+      g_pin_bytes[b->device] += b->bytes;
+      return;
+    }
+  }
+  RelaxedCapture relaxed;
+  (void)hipEventSynchronize(b->ev);  // device work may still use it
+  (void)hipEventDestroy(b->ev);
+  (void)hipHostFree(b->host);
+  delete b;
+}
+
 Trace::~Trace() {
-  if (err_ev) (void)hipEventDestroy(err_ev);
-  if (err_host) (void)hipHostFree(err_host);
+  if (err_pin) pin_give(err_pin);  // (kv_trace_free has waited for the device)
 }
 
 kv_status check_device_error(Trace& t, bool wait, const char* who) {
   if (!t.err_pending) return KV_OK;
   if (wait) {
-    KV_HIP(hipEventSynchronize(t.err_ev));
+    KV_HIP(hipEventSynchronize(t.err_pin->ev));
   } else {
-    const hipError_t q = hipEventQuery(t.err_ev);
+    const hipError_t q = hipEventQuery(t.err_pin->ev);
     if (q == hipErrorNotReady) return KV_OK;  // that call is still running
     if (q != hipSuccess) return hip_fail(q, "hipEventQuery");
   }
@@ -264,7 +341,12 @@ kv_status validate_configs(const Trace& t, const kv_config* cfg, uint32_t n_cfg,
   const uint64_t wmax = t.st.w_max;
   for (uint32_t c = 0; c < n_cfg; ++c) {
     const kv_config& C = cfg[c];
-    const std::string at = "kv_eval_configs: config " + std::to_string(c) + ": ";
+    const struct {  // the message's start, made only for a message
+      uint32_t c;
+      std::string operator+(const char* what) const {
+        return "kv_eval_configs: config " + std::to_string(c) + ": " + what;
+      }
+    } at{c};
     if (C.mode > KV_MODE_INCLUSIVE_PREFIX) return fail(KV_ERR_INVALID, at + "unknown mode");
     if (C.partitioned > 1) return fail(KV_ERR_INVALID, at + "partitioned must be 0 or 1");
     for (int r = 0; r < 4; ++r)
@@ -352,9 +434,9 @@ void finish_set(ThresholdSet& ts, std::vector<std::vector<uint32_t>>& per_group,
 
 // The disk TTL tiers' bins: per group its sorted distinct TTL values, the
 // joint histograms' layout (bins of group g: (capacities + 1) x (TTLs + 1)),
-// the histograms' memory.  Needs the shared threshold set built.
-kv_status plan_joint(Trace& t, std::vector<std::vector<double>>& per_group, JointArgs& ja,
-                     JointView& jv, hipStream_t s) {
+// the histograms' memory.  Needs the shared threshold set built; the tables
+// go to the device with the batch's others.
+kv_status plan_joint(Trace& t, std::vector<std::vector<double>>& per_group, JointArgs& ja) {
   const uint32_t G = t.n_groups;
   TtlSet& ts = t.ttl_ts;
   ts.values.clear();
@@ -383,48 +465,30 @@ kv_status plan_joint(Trace& t, std::vector<std::vector<double>>& per_group, Join
     t.joint_stage[2 * nt + G + 1 + g] = jbase[g];
   }
   kv_status st;
-  DevBuf& bt = t.ws[27];
   DevBuf& bh = t.ws[28];
-  if ((st = bt.reserve(t.joint_stage.size() * 4)) != KV_OK) return st;
   const uint64_t hwords = 4ull * nj + nt + G;
   if ((st = bh.reserve(hwords * 8)) != KV_OK) return st;
-  KV_HIP(hipMemcpyAsync(bt.p, t.joint_stage.data(), t.joint_stage.size() * 4,
-                        hipMemcpyHostToDevice, s));
-  ja.tthr = bt.as<double>();
-  ja.toff = bt.as<uint32_t>() + 2 * nt;
-  ja.jbase = ja.toff + G + 1;
   ja.n_tthr = nt;
   ja.n_joint = nj;
   ja.jh = bh.as<uint64_t>();
   ja.fh = ja.jh + 2ull * nj;
   ja.wd = reinterpret_cast<double*>(ja.fh + 2ull * nj);
-  jv.tthr = ja.tthr;
-  jv.toff = ja.toff;
-  jv.jbase = ja.jbase;
-  jv.jh = ja.jh;
-  jv.fh = ja.fh;
-  jv.wd = ja.wd;
   return KV_OK;
 }
 
 struct StackSlot {
-  int ws_thr, ws_hist, ws_phist;  // ws_phist < 0: no prefix-reuse histogram
+  int ws_hist, ws_phist;  // ws_phist < 0: no prefix-reuse histogram
 };
 
-kv_status run_stack(Trace& t, Order& o, bool partitioned, ThresholdSet& ts, StackSlot slot,
-                    OrderView& view, OrderView& pview, const JointArgs* ja, const uint8_t* real,
-                    hipStream_t s) {
+// thr: the set's thresholds and offsets on the device.
+kv_status run_stack(Trace& t, Order& o, bool partitioned, ThresholdSet& ts, const uint32_t* thr,
+                    StackSlot slot, OrderView& view, OrderView& pview, const JointArgs* ja,
+                    const uint8_t* real, hipStream_t s) {
   kv_status st;
-  DevBuf& bt = t.ws[slot.ws_thr];
   DevBuf& bh = t.ws[slot.ws_hist];
-  const uint64_t nthr = ts.values.size();
-  if ((st = bt.reserve((nthr + KV_MAX_GROUPS + 1) * 4)) != KV_OK) return st;
   const uint64_t nbins = ts.total_bins();
   if ((st = bh.reserve(nbins * 4 * 8)) != KV_OK) return st;
-  uint32_t* thr = bt.as<uint32_t>();
-  uint32_t* off = thr + nthr;
-  if (nthr) KV_HIP(hipMemcpyAsync(thr, ts.values.data(), nthr * 4, hipMemcpyHostToDevice, s));
-  KV_HIP(hipMemcpyAsync(off, ts.off, (KV_MAX_GROUPS + 1) * 4, hipMemcpyHostToDevice, s));
+  const uint32_t* off = thr + ts.values.size();
   uint64_t* ph = nullptr;
   if (slot.ws_phist >= 0) {
     DevBuf& bp = t.ws[slot.ws_phist];
@@ -440,6 +504,60 @@ kv_status run_stack(Trace& t, Order& o, bool partitioned, ThresholdSet& ts, Stac
   pview = view;
   if (ph) pview.hist = ph;
   return KV_OK;
+}
+
+// One table of an upload, and the room it takes on the device.
+struct Piece {
+  const void* p;
+  uint64_t bytes;
+  uint64_t room() const { return (bytes + 255) & ~255ull; }
+};
+
+// Copies tables to the device, one after another (each on a multiple of 256
+// bytes): through pinned memory that a kernel reads, or, past kUploadPin
+// bytes and while the stream is captured (a graph reads the host memory again
+// each time it runs), by one copy from `stage`, memory of the trace.  The
+// pieces may be changed once the call returns.
+// Pageable copies of a few KB, up to five in a call, kept the host waiting:
+// its part of a small batch's call took 86 us, now 53 (search batches 97 -> 40).
+constexpr uint64_t kUploadPin = 1u << 20;
+
+kv_status upload(std::vector<uint8_t>& stage, uint8_t* dst, const std::vector<Piece>& pieces,
+                 hipStream_t s) {
+  uint64_t bytes = 0;
+  for (const Piece& p : pieces) bytes += p.room();
+  PinBlock* pin = nullptr;
+  uint8_t* host;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess) {
+    (void)hipGetLastError();  // (the legacy stream beside another's capture)
+    cap = hipStreamCaptureStatusActive;
+  }
+  if (bytes <= kUploadPin && cap == hipStreamCaptureStatusNone) {
+    if (kv_status st = pin_take(bytes, &pin)) return st;
+    host = pin->host;
+  } else {
+    stage.resize(bytes);
+    host = stage.data();
+  }
+  uint64_t at = 0;
+  for (const Piece& p : pieces) {
+    std::memcpy(host + at, p.p, p.bytes);
+    at += p.room();
+  }
+  if (!pin) {
+    KV_HIP(hipMemcpyAsync(dst, host, bytes, hipMemcpyHostToDevice, s));
+    return KV_OK;
+  }
+  kv_status st = copy_words(pin->dev, dst, bytes, s);
+  const hipError_t e = hipEventRecord(pin->ev, s);
+  if (e != hipSuccess) {
+    // no telling when the kernel is done with the block: it is not reused
+    (void)hipGetLastError();
+    return st != KV_OK ? st : hip_fail(e, "hipEventRecord");
+  }
+  pin_give(pin);
+  return st;
 }
 
 // What kv_pareto's counting calls share, one set per device, kept until the
@@ -534,18 +652,16 @@ kv_status kv_trace_load(const kv_trace_desc* d, void* stream, kv_trace** out) {
   hipStream_t s = (hipStream_t)stream;
   Trace* t = new Trace();
   KV_HIP(hipGetDevice(&t->device));
-  kv_status st = canon_build(*t, *d, s);
+  kv_status st = t->err.reserve(2 * sizeof(uint32_t));
+  if (st == KV_OK) st = pin_take(4096, &t->err_pin);
+  if (st == KV_OK) {
+    t->err_host = reinterpret_cast<uint32_t*>(t->err_pin->host);
+    st = canon_build(*t, *d, s);
+  }
   if (st == KV_OK && t->st.n_w >= 0xFFFFFFFFull) {
     st = fail(KV_ERR_UNSUPPORTED, "kv_trace_load: total weight must stay below 2^32 granules");
   }
-  if (st == KV_OK) st = t->err.reserve(2 * sizeof(uint32_t));
-  if (st == KV_OK) st = fill_u32(t->err.as<uint32_t>(), 0, 2, s);
-  if (st == KV_OK) {
-    hipError_t e = hipHostMalloc((void**)&t->err_host, 2 * sizeof(uint32_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&t->err_ev, hipEventDisableTiming);
-    if (e != hipSuccess) st = hip_fail(e, "kv_trace_load: error record");
-    else t->err_host[0] = t->err_host[1] = 0;
-  }
+  if (st == KV_OK) t->err_host[0] = t->err_host[1] = 0;
   if (st != KV_OK) {
     (void)hipStreamSynchronize(s);
     delete t;
@@ -580,12 +696,11 @@ kv_status kv_ttl_curves(const kv_trace* h, const double* ttl, uint32_t n_ttl, ui
   if ((uint64_t)t->n_groups * ((uint64_t)n_ttl + 1) > 4096)
     return fail(KV_ERR_UNSUPPORTED, "kv_ttl_curves: n_groups * (n_ttl + 1) must be <= 4096");
   hipStream_t s = (hipStream_t)stream;
-  // the thresholds are staged in the trace so they outlive the async copy
-  t->ttl_stage.assign(ttl, ttl + n_ttl);
   DevBuf& bt = t->ws[23];
   kv_status st;
-  if ((st = bt.reserve((uint64_t)n_ttl * 8)) != KV_OK) return st;
-  KV_HIP(hipMemcpyAsync(bt.p, t->ttl_stage.data(), (uint64_t)n_ttl * 8, hipMemcpyHostToDevice, s));
+  const Piece piece{ttl, (uint64_t)n_ttl * 8};
+  if ((st = bt.reserve(piece.room())) != KV_OK) return st;
+  if ((st = upload(t->ttl_stage, bt.as<uint8_t>(), {piece}, s)) != KV_OK) return st;
   return ttl_curves(*t, bt.as<double>(), n_ttl, hits, hitw, store, s);
 }
 
@@ -670,8 +785,6 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
     }
   }
   const uint32_t G = t->n_groups;
-  t->cfg_stage.assign(cfg, cfg + n_cfg);
-
   // ---- plan: thresholds per order, replay jobs
   std::vector<std::vector<uint32_t>> tsh(G), tpt(G), tlf(G);
   std::vector<std::vector<double>> tttl(G);  // disk TTL values per group
@@ -743,17 +856,51 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
     j.end = j.order ? o.seg[j.group + 1] : t->n;
   }
 
-  // ---- device copies of the batch and per-group statistics
-  DevBuf& bcfg = t->ws[9];
-  DevBuf& bgs = t->ws[10];
-  if ((st = bcfg.reserve((uint64_t)n_cfg * sizeof(kv_config))) != KV_OK) return st;
-  if ((st = bgs.reserve(sizeof(GroupStats) * KV_MAX_GROUPS)) != KV_OK) return st;
+  // ---- the batch, per-group statistics and lookup tables, copied at once
+  JointArgs ja;
+  if (need_shared) finish_set(t->shared_ts, tsh, G);
+  if (need_leaf) finish_set(t->leaf_ts, tlf, G);
+  if (need_part) finish_set(t->part_ts, tpt, G);
+  if (need_joint && (st = plan_joint(*t, tttl, ja)) != KV_OK) return st;
+  GroupStats gs[KV_MAX_GROUPS];
   for (uint32_t g = 0; g < KV_MAX_GROUPS; ++g)
-    t->gs_stage[g] = GroupStats{t->st.n_g[g], t->st.n_w_g[g], t->st.u_g[g], w0, t->st.u_w_g[g]};
-  KV_HIP(hipMemcpyAsync(bcfg.p, t->cfg_stage.data(), (uint64_t)n_cfg * sizeof(kv_config),
-                        hipMemcpyHostToDevice, s));
-  KV_HIP(hipMemcpyAsync(bgs.p, t->gs_stage, sizeof(t->gs_stage), hipMemcpyHostToDevice, s));
+    gs[g] = GroupStats{t->st.n_g[g], t->st.n_w_g[g], t->st.u_g[g], w0, t->st.u_w_g[g]};
+  std::vector<Piece> pieces{{cfg, (uint64_t)n_cfg * sizeof(kv_config)}, {gs, sizeof(gs)}};
+  const uint32_t* thr_dev[3] = {nullptr, nullptr, nullptr};
+  const ThresholdSet* sets[3] = {need_shared ? &t->shared_ts : nullptr,
+                                 need_leaf ? &t->leaf_ts : nullptr,
+                                 need_part ? &t->part_ts : nullptr};
+  uint64_t at[3] = {}, joint_at = 0, bytes = 0;
+  for (const Piece& p : pieces) bytes += p.room();
+  for (int q = 0; q < 3; ++q) {
+    if (!sets[q]) continue;
+    at[q] = bytes;
+    // thresholds, then offsets: one table
+    auto& v = t->thr_stage[q];
+    v.assign(sets[q]->values.begin(), sets[q]->values.end());
+    v.insert(v.end(), sets[q]->off, sets[q]->off + KV_MAX_GROUPS + 1);
+    pieces.push_back({v.data(), v.size() * 4});
+    bytes += pieces.back().room();
+  }
+  if (need_joint) {
+    joint_at = bytes;
+    pieces.push_back({t->joint_stage.data(), t->joint_stage.size() * 4});
+    bytes += pieces.back().room();
+  }
+  DevBuf& bcfg = t->ws[9];
+  if ((st = bcfg.reserve(bytes)) != KV_OK) return st;
+  if ((st = upload(t->up_stage, bcfg.as<uint8_t>(), pieces, s)) != KV_OK) return st;
   const kv_config* cfg_dev = bcfg.as<kv_config>();
+  const GroupStats* gs_dev = reinterpret_cast<const GroupStats*>(bcfg.as<uint8_t>() + pieces[0].room());
+  for (int q = 0; q < 3; ++q)
+    thr_dev[q] = reinterpret_cast<const uint32_t*>(bcfg.as<uint8_t>() + at[q]);
+  JointView jv;
+  if (need_joint) {
+    ja.tthr = reinterpret_cast<const double*>(bcfg.as<uint8_t>() + joint_at);
+    ja.toff = reinterpret_cast<const uint32_t*>(ja.tthr) + 2 * ja.n_tthr;
+    ja.jbase = ja.toff + G + 1;
+    jv = JointView{ja.tthr, ja.toff, ja.jbase, ja.jh, ja.fh, ja.wd};
+  }
   double* store_cg = nullptr;  // unbounded disk TTL tiers' storage integrals
   if (need_joint) {
     if ((st = t->ws[29].reserve((uint64_t)n_cfg * G * sizeof(double))) != KV_OK) return st;
@@ -764,30 +911,24 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
   auto lru = [&]() -> kv_status {
     kv_status r;
     OrderView vsh, vpt, vpx, vlf, unused;
-    JointArgs ja;
-    JointView jv;
     if (need_shared) {
-      finish_set(t->shared_ts, tsh, G);
-      if (need_joint && (r = plan_joint(*t, tttl, ja, jv, s)) != KV_OK) return r;
-      if ((r = run_stack(*t, t->shared, false, t->shared_ts,
-                         StackSlot{5, 6, need_prefix ? 24 : -1}, vsh, vpx,
+      if ((r = run_stack(*t, t->shared, false, t->shared_ts, thr_dev[0],
+                         StackSlot{6, need_prefix ? 24 : -1}, vsh, vpx,
                          need_joint ? &ja : nullptr, nullptr, s)) != KV_OK)
         return r;
     }
     if (need_leaf) {
-      finish_set(t->leaf_ts, tlf, G);
-      if ((r = run_stack(*t, t->leaf, false, t->leaf_ts, StackSlot{30, 31, -1}, vlf, unused,
+      if ((r = run_stack(*t, t->leaf, false, t->leaf_ts, thr_dev[1], StackSlot{31, -1}, vlf, unused,
                          nullptr, t->leaf_real.as<uint8_t>(), s)) != KV_OK)
         return r;
     }
     if (need_part) {
-      finish_set(t->part_ts, tpt, G);
-      if ((r = run_stack(*t, t->part, true, t->part_ts, StackSlot{7, 8, -1}, vpt, unused,
+      if ((r = run_stack(*t, t->part, true, t->part_ts, thr_dev[2], StackSlot{8, -1}, vpt, unused,
                          nullptr, nullptr, s)) != KV_OK)
         return r;
     }
     if (need_shared || need_part || need_leaf)
-      return lru_counts(cfg_dev, n_cfg, G, vsh, vpt, vpx, vlf, jv, bgs.as<GroupStats>(), mixed,
+      return lru_counts(cfg_dev, n_cfg, G, vsh, vpt, vpx, vlf, jv, gs_dev, mixed,
                         counts, store_cg, s);
     return KV_OK;
   };
@@ -799,7 +940,7 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
     return st;
   }
   // ---- exclusive hierarchies without a split stack
-  if (need_excl && (st = excl_run(*t, cfg, n_cfg, bgs.as<GroupStats>(), counts, s)) != KV_OK) return st;
+  if (need_excl && (st = excl_run(*t, cfg, n_cfg, gs_dev, counts, s)) != KV_OK) return st;
   // ---- objectives
   if (obj) {
     st = objectives(cfg_dev, n_cfg, G, counts, store_cg, *model, (double)t->gb, (double)t->tpg,

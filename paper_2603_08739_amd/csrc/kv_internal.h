@@ -46,6 +46,18 @@ struct DevBuf {
   T* as() const { return static_cast<T*>(p); }
 };
 
+// A pinned host block from the per-device pool: `ev` is recorded behind the
+// last device work that uses it before it is given back.
+struct PinBlock {
+  uint8_t* host = nullptr;
+  uint8_t* dev = nullptr;   // the same memory by its device address
+  size_t bytes = 0;
+  int device = 0;
+  hipEvent_t ev = nullptr;
+};
+kv_status pin_take(size_t bytes, PinBlock** out);
+void pin_give(PinBlock* b);
+
 // One order of the accesses: the trace order, or the accesses regrouped
 // stably by tenant group (for per-group partitioned caches).
 struct Order {
@@ -126,10 +138,10 @@ struct Trace {
   DevBuf ws[32];
   // Device error record {code, job} written by a replay kernel that fails
   // its internal state check; copied after every kv_eval_configs call that
-  // replays into `err_host` (pinned), with `err_ev` recorded after the copy.
+  // replays into `err_host` (pinned), with err_pin->ev recorded after the copy.
   DevBuf err;
-  uint32_t* err_host = nullptr;
-  hipEvent_t err_ev = nullptr;
+  PinBlock* err_pin = nullptr;
+  uint32_t* err_host = nullptr;  // in err_pin
   bool err_pending = false;
   std::vector<ReplayJobInfo> err_jobs;  // the replayed jobs of the latest call
   ~Trace();
@@ -137,10 +149,9 @@ struct Trace {
   ThresholdSet shared_ts, part_ts, leaf_ts;
   TtlSet ttl_ts;
   std::vector<uint32_t> joint_stage;
-  std::vector<kv_config> cfg_stage;
-  GroupStats gs_stage[KV_MAX_GROUPS];
+  std::vector<uint32_t> thr_stage[3];
+  std::vector<uint8_t> up_stage, ttl_stage;
   std::vector<uint8_t> job_stage, rec_stage, src_stage;
-  std::vector<double> ttl_stage;
   std::vector<unsigned long long> jc_stage;
   std::vector<uint8_t> excl_stage, emit_stage;
 };
@@ -174,6 +185,9 @@ kv_status scan_u32(const uint32_t* in, uint32_t* out, uint64_t m, bool inclusive
                    uint32_t* scratch, hipStream_t s);
 kv_status fill_u32(uint32_t* p, uint32_t v, uint64_t m, hipStream_t s);
 kv_status fill_u64(uint64_t* p, uint64_t v, uint64_t m, hipStream_t s);
+// Copies `bytes` (a multiple of 16, 16-byte aligned) between device addresses,
+// pinned host memory's among them.
+kv_status copy_words(const void* src, void* dst, uint64_t bytes, hipStream_t s);
 
 // canonicalisation (k_canon.hip)
 kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s);
