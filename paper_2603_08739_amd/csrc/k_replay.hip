@@ -286,22 +286,9 @@ __device__ __forceinline__ void store_hits_n(const bool* hit, uint64_t c0, uint3
   }
 }
 
-// Adds per-thread (count, weight) partials of one group: one LDS atomic per
-// wavefront.
-__device__ __forceinline__ void add_uniform(unsigned long long* dc, unsigned long long* dw,
-                                            uint32_t c, uint32_t w) {
-  const uint32_t sc = wave_sum(c), sw = wave_sum(w);
-  if (lane_id() == 0 && sc) {
-    atomicAdd(dc, (unsigned long long)sc);
-    atomicAdd(dw, (unsigned long long)sw);
-  }
-}
-
 struct FifoLds {
   uint8_t ex[kRChunk];
   uint32_t red[2 * kRNW];
-  uint32_t anyflag[2];
-  unsigned long long fin[KV_MAX_GROUPS], finw[KV_MAX_GROUPS];
 };
 
 // Inputs of one chunk for one thread (its kRIt consecutive accesses).
@@ -359,7 +346,14 @@ __device__ __forceinline__ void issue_inputs(const JobDev& j, const JobArgs& a, 
 // once per chunk: at its first access whose insertion total W(i) exceeds
 // S[b] + C.  W depends on the misses before i, and more misses only raise W,
 // so iterating "misses -> W -> misses" from "no misses" rises monotonically
-// to the exact answer.
+// to the exact answer.  The prefix sum that gives W also carries whether any
+// miss changed (from bit kChgBit on), so an iteration has two barriers.
+//
+// A chunk is a serial chain of barriers and cache reads, and its length is
+// bound by the capacity, so short chunks are many; NT is the least number of
+// threads that holds one (256, 512, 1024).  112 jobs over 1.1e7 accesses, the
+// longest with 2300 chunks of 1024: 15.3 ms with 1024 threads, four barriers an
+// iteration and the final pass over the blocks inside; now 7.5.
 //
 // S[b] < 2^32 (weights sum below 2^32); kNoIns32 marks a block never inserted.
 // The chunk loop is software-pipelined: the inputs of chunk k+2 are loaded
@@ -369,8 +363,10 @@ __device__ __forceinline__ void issue_inputs(const JobDev& j, const JobArgs& a, 
 // block ids follow first occurrence, so the lines are few and shared.
 // ---------------------------------------------------------------------------
 constexpr uint32_t kNoIns32 = 0xFFFFFFFFu;
+constexpr int kChgBit = 20;
+static_assert((uint64_t)kRChunk * 255 < (1ull << kChgBit) && kRNT << kChgBit > 0, "");
 
-template <bool kEmit>
+template <int NT, bool kEmit>
 __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
                                              uint32_t* __restrict__ S,
                                              uint64_t* __restrict__ bits, GroupCounters& gc,
@@ -389,10 +385,8 @@ __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
 #pragma unroll
     for (int e = 0; e < kRIt; ++e) sa[e] = v[e] ? S[A.b[e]] : kNoIns32;
   }
-  if (tid < 2) F.anyflag[tid] = 0;
-  __syncthreads();
-  BlockAny block_any{F.anyflag, 0};
   uint32_t W0 = 0;
+  unsigned long long ci = 0, cw = 0;  // insertions of a job of one group
   for (uint64_t c0 = cstart; c0 < j.end; c0 += L) {
     bool v[kRIt], vb[kRIt], miss[kRIt];
     chunk_valid(j, c0, L, v);
@@ -412,37 +406,43 @@ __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
       ww[e] = (A.w >> (8 * e)) & 0xFFu;
       miss[e] = false;
     }
-    uint32_t tot = 0;
-    for (uint32_t it = 0; it < L + 2; ++it) {
-      uint32_t x = 0;
+    uint32_t tot = 0, chg = 0;
 #pragma unroll
-      for (int e = 0; e < kRIt; ++e) x += miss[e] ? ww[e] : 0u;
-      const uint32_t pre = block_excl_scan_u32<kRNT>(x, F.red, tot);
-      uint32_t run = W0 + pre;
+    for (int e = 0; e < kRIt; ++e) wi[e] = W0;
+    for (uint32_t it = 0; it < L + 2; ++it) {
       uint32_t exw = 0;
 #pragma unroll
       for (int e = 0; e < kRIt; ++e) {
-        wi[e] = run;
-        const bool ex = v[e] && (sa[e] == kNoIns32 || (uint64_t)(run - sa[e]) > j.cap);
+        const bool ex = v[e] && (sa[e] == kNoIns32 || (uint64_t)(wi[e] - sa[e]) > j.cap);
         exw |= (ex ? 1u : 0u) << (8 * e);
-        run += miss[e] ? ww[e] : 0u;
       }
       *reinterpret_cast<uint32_t*>(&F.ex[l0]) = exw;
       __syncthreads();
-      bool changed = false;
+      chg = 0;
+      uint32_t x = 0;
 #pragma unroll
       for (int e = 0; e < kRIt; ++e) {
         const bool ex = (exw >> (8 * e)) & 1u;
         const bool nm = ex && (lp[e] < 0 || F.ex[lp[e]] == 0);
-        changed |= nm != miss[e];
+        chg |= nm != miss[e];
         miss[e] = nm;
+        x += nm ? ww[e] : 0u;
       }
-      const bool again = block_any(changed);
-      if (!again) break;
+      // (no barrier behind the sum: the one above keeps its words apart)
+      const uint32_t pre =
+          block_excl_scan_u32<NT, false>(x | (chg << kChgBit), F.red, tot) & ((1u << kChgBit) - 1);
+      uint32_t run = W0 + pre;
+#pragma unroll
+      for (int e = 0; e < kRIt; ++e) {
+        wi[e] = run;
+        run += miss[e] ? ww[e] : 0u;
+      }
+      chg = tot >> kChgBit;
+      tot &= (1u << kChgBit) - 1;
+      if (!chg) break;
     }
     // tot and wi belong to the final miss set
     bool hit[kRIt];
-    uint32_t ci = 0, cw = 0;
 #pragma unroll
     for (int e = 0; e < kRIt; ++e) {
       hit[e] = v[e] && !miss[e];
@@ -459,7 +459,6 @@ __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
         }
       }
     }
-    if (g1) add_uniform(&gc.ins[g0], &gc.insw[g0], ci, cw);
     W0 += tot;
     store_hits(hit, c0, L, j, bits);
     __syncthreads();
@@ -475,48 +474,20 @@ __device__ __forceinline__ void fifo_chunked(const JobDev& j, const JobArgs& a,
 #pragma unroll
     for (int e = 0; e < kRIt; ++e) sa[e] = sb[e];
   }
-  // evictions = insertions - blocks still queued at the end.  The pass over
-  // every block's state is bound by load latency: each thread keeps kEndU
-  // loads in flight, and with one group the queued blocks add up in
-  // registers (LDS atomics on one address are taken one lane at a time).
-  if (tid < KV_MAX_GROUPS) F.fin[tid] = F.finw[tid] = 0;
-  __syncthreads();
-  constexpr int kEndU = 8;
-  unsigned long long fc = 0, fw = 0;
-  for (uint64_t b0 = tid; b0 < a.u; b0 += (uint64_t)kRNT * kEndU) {
-    uint32_t s[kEndU], bw[kEndU], bg[kEndU];
-#pragma unroll
-    for (int q = 0; q < kEndU; ++q) {
-      const uint64_t b = b0 + (uint64_t)q * kRNT;
-      const bool in = b < a.u;
-      s[q] = in ? S[b] : kNoIns32;
-      bw[q] = in ? a.blk_w[b] : 0u;
-      bg[q] = in ? a.blk_g[b] : 0u;
-    }
-#pragma unroll
-    for (int q = 0; q < kEndU; ++q) {
-      if (s[q] == kNoIns32 || (uint64_t)(W0 - s[q]) > j.cap) continue;
-      if (g1) {
-        ++fc;
-        fw += bw[q];
-      } else {
-        atomicAdd(&F.fin[bg[q]], 1ull);
-        atomicAdd(&F.finw[bg[q]], (unsigned long long)bw[q]);
-      }
-    }
-  }
   if (g1) {
-    fc = wave_sum(fc);
-    fw = wave_sum(fw);
-    if (lane_id() == 0 && fc) {
-      atomicAdd(&F.fin[g0], fc);
-      atomicAdd(&F.finw[g0], fw);
+    ci = wave_sum(ci);
+    cw = wave_sum(cw);
+    if (lane_id() == 0 && ci) {
+      atomicAdd(&gc.ins[g0], ci);
+      atomicAdd(&gc.insw[g0], cw);
     }
   }
   __syncthreads();
+  // every insertion counts as evicted until k_fifo_end takes off the blocks
+  // that are still queued
   if (tid < KV_MAX_GROUPS) {
-    gc.ev[tid] = gc.ins[tid] - F.fin[tid];
-    gc.evw[tid] = gc.insw[tid] - F.finw[tid];
+    gc.ev[tid] = gc.ins[tid];
+    gc.evw[tid] = gc.insw[tid];
   }
 }
 
@@ -1857,13 +1828,84 @@ __global__ __launch_bounds__(kRNT) void k_replay(const JobDev* __restrict__ jobs
   const bool g1 = a.n_groups == 1 || j.group != KV_MAX_GROUPS;
   const uint32_t g0 = j.group == KV_MAX_GROUPS ? 0u : j.group;
   unsigned long long* cnt = jcnt + (uint64_t)blockIdx.x * a.n_groups * 4;
-  if (j.kind == kJobFifoChunk)
-    fifo_chunked<kEmit>(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), bits + j.bits_off, gc,
-                        lds, g1, g0);
-  else
-    fifo_serial<kEmit>(j, a, reinterpret_cast<uint32_t*>(state + j.state_off), bits + j.bits_off, gc);
+  // (wavefronts that have ended are not waited for at barriers)
+  uint32_t* S = reinterpret_cast<uint32_t*>(state + j.state_off);
+  if (j.kind == kJobFifoChunk && j.chunk <= kRChunk / 4) {
+    if (tid >= kRNT / 4) return;
+    fifo_chunked<kRNT / 4, kEmit>(j, a, S, bits + j.bits_off, gc, lds, g1, g0);
+  } else if (j.kind == kJobFifoChunk && j.chunk <= kRChunk / 2) {
+    if (tid >= kRNT / 2) return;
+    fifo_chunked<kRNT / 2, kEmit>(j, a, S, bits + j.bits_off, gc, lds, g1, g0);
+  } else if (j.kind == kJobFifoChunk) {
+    fifo_chunked<kRNT, kEmit>(j, a, S, bits + j.bits_off, gc, lds, g1, g0);
+  } else
+    fifo_serial<kEmit>(j, a, S, bits + j.bits_off, gc);
   __syncthreads();
   write_counters(gc, a.n_groups, cnt);
+}
+
+// The evictions of the chunked FIFO jobs: their insertions less the blocks
+// still queued at the end.  A pass over every block's state, kept out of the
+// replay: there a job's one workgroup waits for it, here the chip shares it.
+constexpr int kEndNT = 256, kEndU = 8;
+__global__ __launch_bounds__(kEndNT) void k_fifo_end(const JobDev* __restrict__ jobs, JobArgs a,
+                                                     const uint64_t* __restrict__ state,
+                                                     unsigned long long* __restrict__ jcnt) {
+  __shared__ unsigned long long fin[KV_MAX_GROUPS], finw[KV_MAX_GROUPS];
+  const uint32_t tid = threadIdx.x;
+  if (blockIdx.y < a.job_lo || blockIdx.y >= a.job_hi) return;
+  const JobDev& j = jobs[blockIdx.y];
+  if (j.closed || j.kind != kJobFifoChunk) return;
+  const uint32_t* S = reinterpret_cast<const uint32_t*>(state + j.state_off);
+  const bool g1 = a.n_groups == 1 || j.group != KV_MAX_GROUPS;
+  unsigned long long* cnt = jcnt + (uint64_t)blockIdx.y * a.n_groups * 4;
+  if (tid < KV_MAX_GROUPS) fin[tid] = finw[tid] = 0;
+  uint32_t W0 = 0;  // the job's inserted weight
+  for (uint32_t g = 0; g < a.n_groups; ++g) W0 += (uint32_t)cnt[g * 4 + 1];
+  __syncthreads();
+  unsigned long long fc = 0, fw = 0;
+  for (uint64_t b0 = (uint64_t)blockIdx.x * kEndNT * kEndU + tid; b0 < a.u;
+       b0 += (uint64_t)gridDim.x * kEndNT * kEndU) {
+    uint32_t s[kEndU], bw[kEndU], bg[kEndU];
+#pragma unroll
+    for (int q = 0; q < kEndU; ++q) {
+      const uint64_t b = b0 + (uint64_t)q * kEndNT;
+      const bool in = b < a.u;
+      s[q] = in ? S[b] : kNoIns32;
+      bw[q] = in ? a.blk_w[b] : 0u;
+      bg[q] = in && !g1 ? a.blk_g[b] : 0u;
+    }
+#pragma unroll
+    for (int q = 0; q < kEndU; ++q) {
+      if (s[q] == kNoIns32 || (uint64_t)(W0 - s[q]) > j.cap) continue;
+      if (g1) {
+        ++fc;
+        fw += bw[q];
+      } else {
+        atomicAdd(&fin[bg[q]], 1ull);
+        atomicAdd(&finw[bg[q]], (unsigned long long)bw[q]);
+      }
+    }
+  }
+  if (g1) {
+    const uint32_t g0 = j.group == KV_MAX_GROUPS ? 0u : j.group;
+    fc = wave_sum(fc);
+    fw = wave_sum(fw);
+    if (lane_id() == 0 && fc) {
+      atomicAdd(&fin[g0], fc);
+      atomicAdd(&finw[g0], fw);
+    }
+  }
+  __syncthreads();
+  if (tid < a.n_groups && fin[tid]) {
+    atomicAdd(cnt + tid * 4 + 2, 0ull - fin[tid]);
+    atomicAdd(cnt + tid * 4 + 3, 0ull - finw[tid]);
+  }
+}
+
+// Workgroups of k_fifo_end per job.
+uint32_t fifo_end_grid(uint64_t u) {
+  return (uint32_t)std::min<uint64_t>((u + kEndNT * kEndU - 1) / (kEndNT * kEndU), 64);
 }
 
 // LFU jobs, NT threads per job; G1: the jobs whose accesses all belong to
@@ -2371,8 +2413,11 @@ kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab,
     else if (k == 1)
       hipLaunchKernelGGL((k_replay_lfu<kLfuNT, false, true>), dim3(nj), dim3(kLfuNT), 0, sk, jd, a,
                          state, cls, state, jcnt);
-    else
+    else {
       hipLaunchKernelGGL(k_replay<true>, dim3(nj), dim3(kRNT), 0, sk, jd, a, state, state, jcnt);
+      hipLaunchKernelGGL(k_fifo_end, dim3(fifo_end_grid(t.u), nj), dim3(kEndNT), 0, sk, jd, a, state,
+                         jcnt);
+    }
     KV_HIP(hipGetLastError());
     KV_HIP(hipEventRecord(aux->join[k], sk));
   }
@@ -2697,10 +2742,14 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
       hipLaunchKernelGGL((k_replay_lfu<kLfuNT, false, false>), dim3(nj), dim3(kLfuNT), 0, sk,
                          bj.as<JobDev>(), x, bstate.as<uint64_t>(), bcls.as<uint32_t>(),
                          bbits.as<uint64_t>(), bjc.as<unsigned long long>());
-    else
+    else {
       hipLaunchKernelGGL(k_replay<false>, dim3(nj), dim3(kRNT), 0, sk, bj.as<JobDev>(), x,
                          bstate.as<uint64_t>(), bbits.as<uint64_t>(),
                          bjc.as<unsigned long long>());
+      KV_HIP(hipGetLastError());
+      hipLaunchKernelGGL(k_fifo_end, dim3(fifo_end_grid(t.u), nj), dim3(kEndNT), 0, sk,
+                         bj.as<JobDev>(), x, bstate.as<uint64_t>(), bjc.as<unsigned long long>());
+    }
     KV_HIP(hipGetLastError());
     tm.reset();
     return KV_OK;
