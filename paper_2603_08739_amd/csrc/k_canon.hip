@@ -42,6 +42,9 @@ constexpr int kPtBits = 9;                       // most bits of a partition dig
 constexpr uint32_t kPtDigits = 1u << kPtBits;
 constexpr int kLkBits = 10;                      // slots of the linking table
 constexpr uint32_t kLkSlots = 1u << kLkBits;
+// A table with more blocks is emptied at the next stretch (one that starts
+// inside a row may add the row's blocks first: a quarter at most is in use)
+constexpr uint32_t kLkClear = kLkSlots / 4 - 64;
 
 enum : uint32_t {
   kErrGroup = 1u,
@@ -333,9 +336,11 @@ __global__ __launch_bounds__(kRsNT) void k_pt_scatter(const uint64_t* __restrict
 // at a time: each finds its block's slot in an LDS hash table, its previous
 // access is the latest lower lane of that slot or the slot's latest position.
 // out[k] = (previous position + 1 or 0, position of the block's first access).
-// The table is cleared between stretches once it fills up; bound by the chain
+// The table is emptied between stretches once it fills up; bound by the chain
 // of LDS operations per 64 elements, with eight wavefronts (20 KB each) to a
-// compute unit (1.09e8 accesses: 2.0 ms).
+// compute unit.  Rows were cut where a stretch ended, and the next one loaded
+// from there; they are now taken whole and loaded two ahead (1.09e8 accesses:
+// 2.03 -> 1.67 ms, 4.6e6: 114 -> 79 us).
 __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
                                                 const uint32_t* __restrict__ V, uint32_t n,
                                                 int bits, uint32_t chunk,
@@ -372,73 +377,95 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
       if (at >= c1) return;
     }
   }
+  // rows of 64, two loaded ahead.  A row is taken whole, whatever stretches it
+  // spans; it is cut only where the table is emptied and where the chunk's
+  // last stretch ends.
   uint32_t occ = 0, most = 0;
-  uint64_t kn = at + lane < n ? K[at + lane] : 0ull;
-  uint32_t vn = at + lane < n ? V[at + lane] : 0u;
-  uint64_t cur = ~0ull;  // the stretch's digit (none yet: no digit has 64 bits)
-  for (;;) {
-    const uint64_t k = kn;
-    const uint32_t v = vn;
+  const auto ldk = [&](uint32_t i) { return K[min(i, n - 1)]; };
+  const auto ldv = [&](uint32_t i) { return V[min(i, n - 1)]; };
+  uint64_t k = ldk(at + lane), k1 = ldk(at + 64 + lane);
+  uint32_t v = ldv(at + lane), v1 = ldv(at + 64 + lane);
+  uint64_t prev = ~0ull;  // the digit before the row (none yet: no digit has 64 bits)
+  for (; at < n; at += 64) {
     const uint32_t i = at + lane;
-    // the next 64, ahead of this row's work
-    kn = i + 64 < n ? K[i + 64] : 0ull;
-    vn = i + 64 < n ? V[i + 64] : 0u;
+    const uint64_t k2 = ldk(i + 128);
+    const uint32_t v2 = ldv(i + 128);
     const uint64_t dg = k >> dshift;
-    const uint64_t d0 = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(dg >> 32)) << 32) |
-                        (uint32_t)__builtin_amdgcn_readfirstlane((int)dg);
-    if (d0 != cur) {  // a stretch starts here
-      if (at >= c1) break;
-      cur = d0;
-      if (occ > kLkSlots / 4) {
-        clear();
-        occ = 0;
+    // lanes at which a stretch starts
+    const uint32_t up = (uint32_t)max((int)lane - 1, 0);
+    uint64_t db = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(dg >> 32), (int)up, 64) << 32) |
+                  (uint32_t)__shfl((int)(uint32_t)dg, (int)up, 64);
+    if (lane == 0) db = prev;
+    const uint64_t starts = __ballot(i < n && dg != db);
+    prev = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(dg >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dg, 63);
+    uint64_t row = __ballot(i < n);  // still to be taken
+    bool end = false;
+    if (at + 64 > c1) {
+      const uint64_t out_of = at >= c1 ? starts : starts & (~0ull << (c1 - at));
+      if (out_of) {
+        row &= (1ull << __builtin_ctzll(out_of)) - 1;
+        end = true;
       }
     }
-    const uint64_t mine = __ballot(i < n && dg == cur);  // from lane 0 on
-    const bool in = (mine >> lane) & 1ull;
-    if (occ + 64 > kLkSlots) {  // too many distinct blocks: the load is redone by sorting
-      if (lane == 0) atomicOr(&st->full, 1u);
-      break;
-    }
-    uint32_t s = k == 0ull ? kLkSlots : (uint32_t)(k >> sshift) & (kLkSlots - 1);
-    bool todo = in && k != 0ull, fresh = false;
-    while (__ballot(todo)) {
-      if (todo) {
-        const unsigned long long old = atomicCAS(&key[s], 0ull, (unsigned long long)k);
-        fresh = old == 0ull;
-        if (fresh || old == k) todo = false;
-        else s = (s + 1) & (kLkSlots - 1);
+    while (row) {
+      uint64_t mine = row;
+      if (occ > kLkClear) {
+        const uint64_t b = starts & row;
+        if (b) {
+          mine = row & ((1ull << __builtin_ctzll(b)) - 1);
+          if (!mine) {  // the stretch starts here
+            clear();
+            occ = 0;
+            mine = row;
+          }
+        }
       }
-    }
-    occ += (uint32_t)__popcll(__ballot(fresh));
-    uint64_t peers = mine;
+      row &= ~mine;
+      const bool in = (mine >> lane) & 1ull;
+      if (occ + 64 > kLkSlots) {  // too many distinct blocks: the load is redone by sorting
+        if (lane == 0) atomicOr(&st->full, 1u);
+        end = true;
+        break;
+      }
+      uint32_t s = k == 0ull ? kLkSlots : (uint32_t)(k >> sshift) & (kLkSlots - 1);
+      bool todo = in && k != 0ull, fresh = false;
+      while (__ballot(todo)) {
+        if (todo) {
+          const unsigned long long old = atomicCAS(&key[s], 0ull, (unsigned long long)k);
+          fresh = old == 0ull;
+          if (fresh || old == k) todo = false;
+          else s = (s + 1) & (kLkSlots - 1);
+        }
+      }
+      occ += (uint32_t)__popcll(__ballot(fresh));
+      uint64_t peers = mine;
 #pragma unroll
-    for (int b = 0; b <= kLkBits; ++b) {
-      const bool bit = (s >> b) & 1u;
-      const uint64_t bb = __ballot(bit);
-      peers &= bit ? bb : ~bb;
+      for (int b = 0; b <= kLkBits; ++b) {
+        const bool bit = (s >> b) & 1u;
+        const uint64_t bb = __ballot(bit);
+        peers &= bit ? bb : ~bb;
+      }
+      const uint64_t lower = peers & lt;
+      const uint32_t l = in ? last[s] : 0u, f = in ? first[s] : 0u, c = in ? cnt[s] : 0u;
+      const int pl = lower ? 63 - __builtin_clzll(lower) : 0;
+      const int ll = peers ? __builtin_ctzll(peers) : 0;
+      const uint32_t vp = (uint32_t)__shfl((int)v, pl, 64), v0 = (uint32_t)__shfl((int)v, ll, 64);
+      const uint32_t fp = l == kNone ? v0 : f;
+      if (in) out[i] = make_uint2(lower ? vp + 1u : l + 1u, fp);  // kNone + 1 = 0
+      if (in && (peers >> lane) == 1ull) {  // the slot's latest element
+        const uint32_t tot = (l == kNone ? 0u : c) + (uint32_t)__popcll(peers);
+        last[s] = v;
+        first[s] = fp;
+        cnt[s] = tot;
+        most = max(most, tot);
+      }
     }
-    const uint64_t lower = peers & lt;
-    const uint32_t l = in ? last[s] : 0u, f = in ? first[s] : 0u, c = in ? cnt[s] : 0u;
-    const int pl = lower ? 63 - __builtin_clzll(lower) : 0;
-    const int ll = peers ? __builtin_ctzll(peers) : 0;
-    const uint32_t vp = (uint32_t)__shfl((int)v, pl, 64), v0 = (uint32_t)__shfl((int)v, ll, 64);
-    const uint32_t fp = l == kNone ? v0 : f;
-    if (in) out[i] = make_uint2(lower ? vp + 1u : l + 1u, fp);  // kNone + 1 = 0
-    if (in && (peers >> lane) == 1ull) {  // the slot's latest element
-      const uint32_t tot = (l == kNone ? 0u : c) + (uint32_t)__popcll(peers);
-      last[s] = v;
-      first[s] = fp;
-      cnt[s] = tot;
-      most = max(most, tot);
-    }
-    const uint32_t took = (uint32_t)__popcll(mine);
-    at += took;
-    if (at >= n) break;
-    if (took < 64) {
-      kn = at + lane < n ? K[at + lane] : 0ull;
-      vn = at + lane < n ? V[at + lane] : 0u;
-    }
+    if (end) break;
+    k = k1;
+    v = v1;
+    k1 = k2;
+    v1 = v2;
   }
   most = wave_max_u32(most);
   // atomics on one address are taken one at a time: only those that may count
@@ -1079,7 +1106,12 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
     StageTimer tm(kStLoadLinks, s);
     links = reinterpret_cast<uint2*>(K2);  // free now
     // wavefronts enough to fill the chip, of whole stretches
-    const uint32_t chunk = n >= (1ull << 22) ? 2048 : 512;
+    // some 8192 wavefronts, four to each that the chip holds, of 256 to 4096
+    // elements (shorter ones only look for a first stretch).  With 256, 512,
+    // 1024, 2048, 4096: 26, 35, 44, 69, 100 us for 2.4e5 accesses, 90, 79, 82,
+    // 97, 105 us for 4.6e6, 2.29, 2.03, 1.86, 1.76, 1.67 ms for 1.09e8.
+    uint32_t chunk = 256;
+    while (chunk < 4096 && n >= (uint64_t)chunk * 16384) chunk *= 2;
     hipLaunchKernelGGL(k_pt_link, dim3(div_up(n, chunk)), dim3(64), 0, s, K, V, (uint32_t)n, bits,
                        chunk, links, dstats);
     KV_HIP(hipGetLastError());
