@@ -441,11 +441,11 @@ def device_info(torch, copy_gbs):
 
 
 def exclusive_replay(torch, tg, host, K):
-    """Exclusive (write-back demotion) hierarchies that are no split stack,
-    replayed access by access: the tiny workload's 64 configurations as FIFO
-    and as LFU hierarchies, one wavefront walking the trace per
-    configuration.  Bound by the dependent memory accesses of that walk, so
-    the figure is the time per access of one configuration's walk."""
+    """Exclusive (write-back demotion) hierarchies that are no split stack:
+    the tiny workload's 64 configurations as FIFO and as LFU hierarchies.  The
+    top tier of each is replayed once per distinct capacity; one wavefront per
+    configuration then walks the queue of the top tier's demotions.  Bound by
+    that walk's chain, so the figure is its time per access of the trace."""
     rec = tg.recipe("tiny")
     base = tg.configs_for("tiny", rec)
     parts = []
@@ -482,7 +482,7 @@ def exclusive_replay(torch, tg, host, K):
             "policies": "FIFO and LFU, write-back demotion", "avg_launch_ms": per,
             "launches": calls, "value": n * n_cfg / (per / 1000.0),
             "unit": "block-accesses×configs/s", "ns_per_access": per * 1e6 / n,
-            "bound": "dependent memory latency of one lane's walk per configuration"}
+            "bound": "the chain of one wavefront's walk per configuration"}
 
 
 def extras(dev, rec, cfgs, G, model, n, torch, K, ttl_only=False):
