@@ -746,60 +746,72 @@ __global__ __launch_bounds__(256) void k_sd_rstart(const uint32_t* __restrict__ 
 // block of its request up to it is (radix-tree caches reuse a request's
 // longest cached prefix), i.e. the running maximum of the stack distances
 // over the request, D'_i = max(D_j : j <= i in i's request), is at most C.
-// One wavefront per request scans its distances 64 at a time and bins D'
-// into fields 0 and 1 of `ba.hist`.
+// One wavefront per request scans its distances 64 at a time, up to a first
+// access (nothing behind it is reused), and bins D' into fields 0 and 1 of
+// `ba.hist`.  D' only grows along a request, so neighbouring lanes share a
+// bin: the last lane of each run of equal bins adds for the run.  Workgroups
+// add their bins to the same words one after another, so they are few (two to
+// a compute unit), large, and take no more LDS than the bins need: 4.6e6
+// accesses in 1.2e5 requests, 36 us; 123 with 4096 workgroups of 256.
+constexpr int kPfNT = 1024;
 template <bool kLds>
-__global__ __launch_bounds__(256) void k_sd_prefix(const uint32_t* __restrict__ D,
+__global__ __launch_bounds__(kPfNT) void k_sd_prefix(const uint32_t* __restrict__ D,
                                                    const uint32_t* __restrict__ rstart,
                                                    uint32_t n_req, const uint8_t* __restrict__ w8,
                                                    const uint8_t* __restrict__ g8, BinArgs ba) {
-  __shared__ uint32_t sthr[kLds ? kThrLds : 1];
-  __shared__ uint32_t scnt[kLds ? kThrLds + KV_MAX_GROUPS : 1];
-  __shared__ uint32_t sw[kLds ? kThrLds + KV_MAX_GROUPS : 1];
+  extern __shared__ uint32_t sm[];  // kLds: thresholds, counts, weights
   __shared__ uint32_t soff[KV_MAX_GROUPS + 1];
   const uint32_t nbins = ba.n_thr + ba.n_groups;
+  uint32_t *sthr = sm, *scnt = sm + ba.n_thr, *sw = scnt + nbins;
   if (threadIdx.x <= ba.n_groups) soff[threadIdx.x] = ba.off[threadIdx.x];
   if (kLds) {
-    for (uint32_t j = threadIdx.x; j < ba.n_thr; j += 256) sthr[j] = ba.thr[j];
-    for (uint32_t j = threadIdx.x; j < nbins; j += 256) {
+    for (uint32_t j = threadIdx.x; j < ba.n_thr; j += kPfNT) sthr[j] = ba.thr[j];
+    for (uint32_t j = threadIdx.x; j < nbins; j += kPfNT) {
       scnt[j] = 0;
       sw[j] = 0;
     }
   }
   __syncthreads();
   const uint32_t lane = lane_id();
-  const uint32_t waves = gridDim.x * 4;
-  for (uint32_t r = blockIdx.x * 4 + threadIdx.x / 64; r < n_req; r += waves) {
+  const uint32_t waves = gridDim.x * (kPfNT / 64);
+  for (uint32_t r = blockIdx.x * (kPfNT / 64) + threadIdx.x / 64; r < n_req; r += waves) {
     const uint32_t b = rstart[r], e = rstart[r + 1];
     uint32_t carry = 0;
-    for (uint32_t c = b; c < e; c += 64) {
+    for (uint32_t c = b; c < e && carry != kNone; c += 64) {
       const uint32_t i = c + lane;
-      uint32_t m = i < e ? D[i] : 0u;
-#pragma unroll
-      for (int s2 = 1; s2 < 64; s2 <<= 1) {
-        const uint32_t o = (uint32_t)__shfl_up((int)m, s2, 64);
-        if (lane >= (uint32_t)s2) m = max(m, o);
-      }
-      m = max(m, carry);
+      const uint32_t q = min(i, e - 1);
+      uint32_t m = i < e ? D[q] : 0u;
+      const uint32_t g = g8[q], w = w8[q];
+      m = max(wave_incl_max_u32(m), carry);
       carry = (uint32_t)__builtin_amdgcn_readlane((int)m, 63);
-      if (i >= e || m == kNone) continue;   // past the request, or behind a first access
-      const uint32_t g = g8[i];
-      const uint32_t w = w8[i];
-      const uint32_t lo = soff[g], hi = soff[g + 1];
-      if (kLds) {
-        const uint32_t bin = lo + g + (lower_bound(sthr, lo, hi, m) - lo);
-        atomicAdd(&scnt[bin], 1u);
-        atomicAdd(&sw[bin], w);
-      } else {
-        const uint32_t bin = lo + g + (lower_bound(ba.thr, lo, hi, m) - lo);
-        atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 0], 1ull);
-        atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 1], (unsigned long long)w);
+      const bool in = i < e && m != kNone;  // not past the request, nor behind a first access
+      uint32_t bin = kNone;
+      if (in) {
+        const uint32_t lo = soff[g], hi = soff[g + 1];
+        bin = lo + g + (lower_bound(kLds ? (const uint32_t*)sthr : ba.thr, lo, hi, m) - lo);
+      }
+      // `in` holds for the low lanes: a run is `in` in all its lanes or in none
+      const uint32_t before = (uint32_t)__shfl_up((int)bin, 1, 64);
+      const uint64_t heads = __ballot(lane == 0 || bin != before);
+      const uint32_t sum = wave_incl_scan_u32(in ? w : 0u);
+      const uint32_t head = 63u - (uint32_t)__builtin_clzll(heads & (~0ull >> (63u - lane)));
+      const uint32_t sum0 = (uint32_t)__shfl((int)sum, (int)head - 1, 64);
+      const bool last = lane == 63 || ((heads >> (lane + 1)) & 1ull);
+      if (in && last) {
+        const uint32_t cn = lane - head + 1, cw = sum - (head ? sum0 : 0u);
+        if (kLds) {
+          atomicAdd(&scnt[bin], cn);
+          atomicAdd(&sw[bin], cw);
+        } else {
+          atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 0], (unsigned long long)cn);
+          atomicAdd((unsigned long long*)&ba.hist[bin * 4 + 1], (unsigned long long)cw);
+        }
       }
     }
   }
   if (kLds) {
     __syncthreads();
-    for (uint32_t j = threadIdx.x; j < nbins; j += 256) {
+    for (uint32_t j = threadIdx.x; j < nbins; j += kPfNT) {
       if (scnt[j]) {
         atomicAdd((unsigned long long*)&ba.hist[j * 4 + 0], (unsigned long long)scnt[j]);
         atomicAdd((unsigned long long*)&ba.hist[j * 4 + 1], (unsigned long long)sw[j]);
@@ -1028,13 +1040,20 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
                          t.req.as<uint32_t>(), n, nr, rstart);
       KV_HIP(hipGetLastError());
       BinArgs bp{thr_dev, off_dev, (uint32_t)ts.values.size(), ts.n_groups, phist};
-      const uint32_t gp = std::min<uint32_t>(div_up(nr, 4), 4096);
-      if (lds)
-        hipLaunchKernelGGL(k_sd_prefix<true>, dim3(gp), dim3(256), 0, s, (const uint32_t*)dist,
+      // two workgroups to a compute unit: each adds its bins to the same words
+      const uint32_t gp = std::min<uint32_t>(div_up(nr, kPfNT / 64), 512);
+      if (lds) {
+        const uint32_t pbytes = (bp.n_thr + 2 * (bp.n_thr + bp.n_groups)) * 4;
+        if (pbytes > 64 * 1024 &&  // has to be asked for
+            hipFuncSetAttribute(reinterpret_cast<const void*>(k_sd_prefix<true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)pbytes) != hipSuccess)
+          (void)hipGetLastError();
+        hipLaunchKernelGGL(k_sd_prefix<true>, dim3(gp), dim3(kPfNT), pbytes, s, (const uint32_t*)dist,
                            (const uint32_t*)rstart, nr, w8, g8, bp);
-      else
-        hipLaunchKernelGGL(k_sd_prefix<false>, dim3(gp), dim3(256), 0, s, (const uint32_t*)dist,
+      } else {
+        hipLaunchKernelGGL(k_sd_prefix<false>, dim3(gp), dim3(kPfNT), 0, s, (const uint32_t*)dist,
                            (const uint32_t*)rstart, nr, w8, g8, bp);
+      }
       KV_HIP(hipGetLastError());
     }
   }

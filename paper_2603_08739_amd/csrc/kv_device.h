@@ -68,6 +68,17 @@ __device__ __forceinline__ void wave_totals(const uint32_t* sh, int w, uint32_t&
   below = w ? (uint32_t)__builtin_amdgcn_readlane(incl, w - 1) : 0u;
 }
 
+// Inclusive prefix maximum over the 64 lanes via DPP.
+__device__ __forceinline__ uint32_t wave_incl_max_u32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
+  return v;
+}
+
 // Exclusive prefix sums of two 32-bit values over a block of NT threads.
 // `sh` holds 2 * (NT / 64) words of shared memory; two barriers.  With
 // Trail = false the second barrier (which lets the next call reuse `sh`) is
@@ -114,13 +125,7 @@ __device__ __forceinline__ uint32_t wave_add_dpp(uint32_t v) {
 }
 
 __device__ __forceinline__ uint32_t wave_max_dpp(uint32_t v) {
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));
-  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));
-  return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_max_u32(v), 63);
 }
 
 // Whether any thread of the block passes true: one barrier per call.  Two
