@@ -59,7 +59,8 @@ constexpr uint32_t kThrLds = 6144;      // thresholds kept in LDS for binning
 
 __host__ __device__ __forceinline__ uint64_t tri_off(uint64_t x) { return x * (x - 1) / 2; }
 
-// What the pass adds to with atomics, cleared by its first kernel.
+// What the pass adds to with atomics, cleared by its first kernel where that
+// pays (rows_clear).
 struct Zero {
   uint64_t* p[3];
   uint32_t n[3];
@@ -965,12 +966,17 @@ kv_status stack_pass(Trace& t, Order& o, bool partitioned, const ThresholdSet& t
     StageTimer tm(kStStackMatrix, s);
     const uint32_t row_chunk = env_limit("KVCFG_TEST_ROW_CHUNK", kRowChunk, 1);
     Zero z{};
-    z.p[0] = hist;
-    z.n[0] = ts.total_bins() * 4;
-    z.p[1] = phist;
-    z.n[1] = phist ? ts.total_bins() * 4 : 0;
-    z.p[2] = ja ? ja->jh : nullptr;  // jh, fh and wd lie together
-    z.n[2] = ja ? 4 * ja->n_joint + ja->n_tthr + ts.n_groups : 0;
+    const auto clear = [&](int q, uint64_t* p, uint64_t words) -> kv_status {
+      if (!rows_clear(words, G)) return fill_u64(p, 0, words, s);
+      z.p[q] = p;
+      z.n[q] = (uint32_t)words;
+      return KV_OK;
+    };
+    if ((st = clear(0, hist, 4ull * ts.total_bins())) != KV_OK) return st;
+    if (phist && (st = clear(1, phist, 4ull * ts.total_bins())) != KV_OK) return st;
+    // jh, fh and wd lie together
+    if (ja && (st = clear(2, ja->jh, joint_words(ja->n_joint, ja->n_tthr, ts.n_groups))) != KV_OK)
+      return st;
     hipLaunchKernelGGL(k_sd_rowhist, dim3(G), dim3(kRowNT), 0, s, key, nxt, w8,
                        uni ? t.st.w_max : 0u, n, logb, row_chunk,
                        Q, lsum, z);

@@ -466,8 +466,7 @@ kv_status plan_joint(Trace& t, std::vector<std::vector<double>>& per_group, Join
   }
   kv_status st;
   DevBuf& bh = t.ws[28];
-  const uint64_t hwords = 4ull * nj + nt + G;
-  if ((st = bh.reserve(hwords * 8)) != KV_OK) return st;
+  if ((st = bh.reserve(joint_words(nj, nt, G) * 8)) != KV_OK) return st;
   ja.n_tthr = nt;
   ja.n_joint = nj;
   ja.jh = bh.as<uint64_t>();

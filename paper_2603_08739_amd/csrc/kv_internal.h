@@ -113,6 +113,19 @@ struct JointArgs {
   double* wd = nullptr;            // [n_tthr + G] sum of w * gap per (group, gap bin); follows fh
 };
 
+// 64-bit words of jh, fh and wd together.
+inline uint64_t joint_words(uint64_t n_joint, uint64_t n_tthr, uint64_t n_groups) {
+  return 4 * n_joint + n_tthr + n_groups;
+}
+
+// Whether the stack pass's first kernel, of `rows` workgroups, clears a
+// histogram of `words` 64-bit words on its way: 16 words per thread and no
+// more, so that its 32-bit index (steps of `rows` * 1,024) never passes 2^32.
+// Otherwise a fill of its own does; the joint histograms reach 2^33 words.
+inline bool rows_clear(uint64_t words, uint64_t rows) {
+  return words <= (1ull << 30) && words <= rows * 16384;
+}
+
 struct Trace {
   uint64_t magic = 0;
   int device = 0;
