@@ -6,7 +6,7 @@
 // access to the same block, and a dense id per distinct block.
 //
 // Equal hashes only have to meet, in trace order; they need not be sorted.
-// The accesses are partitioned, stably, by 9 to 18 bits of their mixed hash
+// The accesses are partitioned, stably, by 1 to 20 bits of their mixed hash
 // (one or two passes), so that a few hundred consecutive ones share all the
 // accesses of their blocks.  A wavefront then takes such a stretch in order,
 // 64 accesses at a time, through a hash table in LDS that holds each block's
@@ -20,10 +20,12 @@
 // scatter that this replaced took 15.2 ms (4.6e6 accesses: 0.43 and 1.03 ms;
 // 238,313 accesses, 24 launches fewer than eight sort passes: 0.13 and 0.45).
 //
-// A stretch with more distinct blocks than the table holds (hashes made to
-// collide, or close to 2^29 accesses of distinct blocks) sends the load to a
-// stable LSD radix sort of (hash, position) pairs instead, where neighbours
-// are the previous / next occurrences.
+// A stretch with more distinct blocks than the table holds sends the load to
+// a stable LSD radix sort of (hash, position) pairs instead, where neighbours
+// are the previous / next occurrences.  Up to 2^29 accesses that takes hashes
+// made to collide: with 20 bits a stretch of distinct blocks has at most 512
+// on average.  (With at most 18 bits, loads of more than 2.2e8 distinct blocks
+// came to the sort: 3e8 of them took 133 ms, now 24; 5e8 230 ms, now 44.)
 #include <cstdlib>
 
 #include "kv_device.h"
@@ -38,7 +40,7 @@ constexpr uint32_t kRsTile = kRsNT * kRsItems;  // 8192
 constexpr int kRsDigits = 256;                   // 8-bit digits
 constexpr int kRsWaves = kRsNT / 64;
 
-constexpr int kPtBits = 9;                       // most bits of a partition digit
+constexpr int kPtBits = 10;                      // most bits of a partition digit
 constexpr uint32_t kPtDigits = 1u << kPtBits;
 constexpr int kLkBits = 10;                      // slots of the linking table
 constexpr uint32_t kLkSlots = 1u << kLkBits;
@@ -140,7 +142,7 @@ __global__ __launch_bounds__(kRsNT) void k_load_tiles(
       req_out[i] = r[e];
       g8[i] = (uint8_t)g[e];
       w8[i] = (uint8_t)w[e];
-      if (digits > 1) atomicAdd(&h[(uint32_t)(mixed_hash(k[e]) >> shift) & (digits - 1)], 1u);
+      atomicAdd(&h[(uint32_t)(mixed_hash(k[e]) >> shift) & (digits - 1)], 1u);
       if (g[e] != cg) {
         if (cn) {
           atomicAdd(&sn[cg], cn);
@@ -156,9 +158,7 @@ __global__ __launch_bounds__(kRsNT) void k_load_tiles(
       wmax = max(wmax, w[e]);
     }
     __syncthreads();
-    if (threadIdx.x < digits)
-      counts[(uint64_t)threadIdx.x * ntiles + tile] =
-          digits > 1 ? h[threadIdx.x] : (uint32_t)min<uint64_t>(kRsTile, n - base);
+    if (threadIdx.x < digits) counts[(uint64_t)threadIdx.x * ntiles + tile] = h[threadIdx.x];
     __syncthreads();
   }
   if (n_groups == 1) {
@@ -203,7 +203,7 @@ __global__ void k_load_init(DevStats* st, uint32_t* err) {
   if (threadIdx.x == 0) st->w_min = 0xFFFFFFFFu;
 }
 
-// (mixed hash, position) pairs for the radix sort of the fallback.
+// (hash, position) pairs for the radix sort of the fallback.
 __global__ __launch_bounds__(256) void k_sort_pairs(const uint64_t* __restrict__ hash, uint64_t n,
                                                     uint64_t* __restrict__ keys,
                                                     uint32_t* __restrict__ vals) {
@@ -233,11 +233,11 @@ __global__ __launch_bounds__(kRsNT) void k_pt_count(const uint64_t* __restrict__
     counts[(uint64_t)threadIdx.x * ntiles + blockIdx.x] = h[threadIdx.x];
 }
 
-// Stable partition of one tile by a digit of up to 9 bits, given the exclusive
-// digit offsets (as k_rs_scatter; each 64-lane wavefront ranks 64 consecutive
-// items per round by matching digits with ballots).  dst[i]: where element i
-// went.  kFirst: the input is the caller's hashes in trace order.
-template <bool kFirst>
+// Stable partition of one tile by a digit of up to kBits bits, given the
+// exclusive digit offsets (as k_rs_scatter; each 64-lane wavefront ranks 64
+// consecutive items per round by matching digits with ballots).  dst[i]: where
+// element i went.  kFirst: the input is the caller's hashes in trace order.
+template <bool kFirst, int kBits>
 __global__ __launch_bounds__(kRsNT) void k_pt_scatter(const uint64_t* __restrict__ kin,
                                                       const uint32_t* __restrict__ vin,
                                                       uint64_t* __restrict__ kout,
@@ -246,14 +246,16 @@ __global__ __launch_bounds__(kRsNT) void k_pt_scatter(const uint64_t* __restrict
                                                       int shift, uint32_t digits,
                                                       const uint32_t* __restrict__ offsets,
                                                       uint32_t ntiles) {
-  __shared__ uint16_t wcnt[kRsWaves][kPtDigits];
-  __shared__ uint32_t gbase[kPtDigits];   // the digit's first output position, less its tile start
+  constexpr uint32_t kDigits = 1u << kBits;
+  static_assert(kDigits <= kRsNT, "a thread per digit");
+  __shared__ uint16_t wcnt[kRsWaves][kDigits];
+  __shared__ uint32_t gbase[kDigits];   // the digit's first output position, less its tile start
   __shared__ uint32_t red[kRsWaves];
   __shared__ uint64_t sk[kRsTile];
   __shared__ uint32_t sv[kRsTile];
   const int w = threadIdx.x / 64;
   const uint32_t lane = lane_id();
-  for (int d = threadIdx.x; d < kRsWaves * (int)kPtDigits / 2; d += kRsNT)
+  for (int d = threadIdx.x; d < kRsWaves * (int)kDigits / 2; d += kRsNT)
     reinterpret_cast<uint32_t*>(&wcnt[0][0])[d] = 0;
   const uint32_t g0 =
       threadIdx.x < digits ? offsets[(uint64_t)threadIdx.x * ntiles + blockIdx.x] : 0u;
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(kRsNT) void k_pt_scatter(const uint64_t* __restrict
     d[r] = (uint32_t)(k[r] >> shift) & (digits - 1);
     uint64_t peers = __ballot(valid);
 #pragma unroll
-    for (int b = 0; b < kPtBits; ++b) {
+    for (int b = 0; b < kBits; ++b) {
       const bool bit = (d[r] >> b) & 1u;
       const uint64_t bb = __ballot(bit);
       peers &= bit ? bb : ~bb;
@@ -477,7 +479,8 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
 // One partition pass undone: out[i] = in[dst[i]].
 __global__ __launch_bounds__(256) void k_pt_undo(const uint2* __restrict__ in,
                                                  const uint32_t* __restrict__ dst, uint64_t n,
-                                                 uint2* __restrict__ out) {
+                                                 uint2* __restrict__ out, const DevStats* st) {
+  if (st->full) return;
   constexpr int kU = 4;
   for (uint64_t b = (uint64_t)blockIdx.x * (256 * kU) + threadIdx.x; b < n;
        b += (uint64_t)gridDim.x * (256 * kU)) {
@@ -922,10 +925,17 @@ uint32_t grid_of(uint64_t m, uint64_t cap = 32768) {
 // atomics queue on each address.
 constexpr uint64_t kReduceGrid = 1024;
 
-// Test hook, read at every load: KVCFG_TEST_LOAD_SORT=1 takes the radix sort.
+// Test hooks, read at every load: KVCFG_TEST_LOAD_SORT=1 takes the radix sort;
+// KVCFG_TEST_LOAD_BITS lowers the most partition bits, so that a short trace
+// has long stretches.
 bool sort_forced() {
   const char* e = std::getenv("KVCFG_TEST_LOAD_SORT");
   return e && e[0] == '1';
+}
+
+int most_bits() {
+  const char* e = std::getenv("KVCFG_TEST_LOAD_BITS");
+  return e ? std::min(2 * kPtBits, std::max(1, std::atoi(e))) : 2 * kPtBits;
 }
 
 // One stable LSD pass over (keys, vals) on digit `shift`.
@@ -1035,12 +1045,12 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
   if ((st = t.req.reserve(n * 4)) != KV_OK) return st;
   if ((st = t.req_time.reserve((uint64_t)d.n_req * 8)) != KV_OK) return st;
 
-  // Partition bits: stretches of 256 to 512 accesses on average, so that even
-  // distinct blocks fill at most half the linking table, up to two digits of
-  // 9 bits (longer stretches past 2^27 accesses, whose blocks repeat).
+  // Partition bits: stretches of 256 to 512 accesses on average, whose distinct
+  // blocks, with those a stretch may start with, stay below the linking
+  // table's 960; two digits from 10 bits on.
   int bits = 1;
-  while (bits < 2 * kPtBits && (n >> bits) > 512) ++bits;
-  const int hi_bits = bits <= kPtBits ? bits : (bits + 1) / 2, lo_bits = bits - hi_bits;
+  while (bits < most_bits() && (n >> bits) > 512) ++bits;
+  const int hi_bits = bits < kPtBits ? bits : (bits + 1) / 2, lo_bits = bits - hi_bits;
   const uint32_t hi = 1u << hi_bits, lo = 1u << lo_bits;
   const bool two = lo_bits > 0;
   const uint32_t ntiles = div_up(n, kRsTile);
@@ -1085,9 +1095,16 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
       if ((st = scan_u32(cnt, cnt, (uint64_t)ntiles * dg, false, scratch.as<uint32_t>(), s)) !=
           KV_OK)
         return st;
-      hipLaunchKernelGGL(k_pt_scatter<true>, dim3(ntiles), dim3(kRsNT), 0, s, d.hash,
-                         (const uint32_t*)nullptr, K, V, d1.as<uint32_t>(), n,
-                         two ? 64 - bits : 64 - hi_bits, dg, cnt, ntiles);
+      // digits of 10 bits only past 2^27 accesses: their runs of 8 elements a
+      // tile are scattered more slowly
+      const auto scatter = [&](auto narrow, auto wide, uint32_t digits, const uint64_t* kin,
+                               const uint32_t* vin, uint64_t* kout, uint32_t* vout, uint32_t* to,
+                               int shift) {
+        hipLaunchKernelGGL(digits < kPtDigits ? narrow : wide, dim3(ntiles), dim3(kRsNT), 0, s, kin,
+                           vin, kout, vout, to, n, shift, digits, cnt, ntiles);
+      };
+      scatter(k_pt_scatter<true, kPtBits - 1>, k_pt_scatter<true, kPtBits>, dg, d.hash, nullptr, K, V,
+              d1.as<uint32_t>(), two ? 64 - bits : 64 - hi_bits);
       KV_HIP(hipGetLastError());
       if (two) {
         hipLaunchKernelGGL(k_pt_count, dim3(ntiles), dim3(kRsNT), 0, s, K, n, 64 - hi_bits, hi,
@@ -1096,8 +1113,8 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
         if ((st = scan_u32(cnt, cnt, (uint64_t)ntiles * hi, false, scratch.as<uint32_t>(), s)) !=
             KV_OK)
           return st;
-        hipLaunchKernelGGL(k_pt_scatter<false>, dim3(ntiles), dim3(kRsNT), 0, s, K, V, K2, V2,
-                           d2.as<uint32_t>(), n, 64 - hi_bits, hi, cnt, ntiles);
+        scatter(k_pt_scatter<false, kPtBits - 1>, k_pt_scatter<false, kPtBits>, hi, K, V, K2, V2,
+                d2.as<uint32_t>(), 64 - hi_bits);
         KV_HIP(hipGetLastError());
         std::swap(K, K2);
         std::swap(V, V2);
@@ -1120,7 +1137,7 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
     if (two) {
       uint2* back = reinterpret_cast<uint2*>(K);
       hipLaunchKernelGGL(k_pt_undo, dim3(grid_of(div_up(n, 4))), dim3(256), 0, s, links,
-                         d2.as<uint32_t>(), n, back);
+                         d2.as<uint32_t>(), n, back, dstats);
       KV_HIP(hipGetLastError());
       std::swap(links, back);
       fbits = reinterpret_cast<uint64_t*>(back);
