@@ -47,6 +47,8 @@ constexpr uint32_t kLkSlots = 1u << kLkBits;
 // A table with more blocks is emptied at the next stretch (one that starts
 // inside a row may add the row's blocks first: a quarter at most is in use)
 constexpr uint32_t kLkClear = kLkSlots / 4 - 64;
+constexpr uint32_t kPiece = 8192;                // a long stretch is cut at multiples of this
+constexpr uint32_t kJoinCuts = 16;               // such multiples a joining wavefront looks at
 
 enum : uint32_t {
   kErrGroup = 1u,
@@ -333,6 +335,62 @@ __global__ __launch_bounds__(kRsNT) void k_pt_scatter(const uint64_t* __restrict
   }
 }
 
+// What the blocks of each part of a cut stretch leave to the joining pass: one
+// entry per block at [part * kPiece ..], their number in count[part].
+struct PtLists {
+  uint32_t *elem, *last, *cnt;  // its first element there, its latest position, its accesses
+  uint32_t* count;
+};
+
+// Whether a stretch is cut at m, a multiple of kPiece: it reaches back a whole
+// piece and more (equal top bits are consecutive).
+__device__ __forceinline__ bool pt_cut(const uint64_t* __restrict__ K, uint32_t n, int dshift,
+                                       uint32_t m) {
+  return m >= kPiece && m < n && (K[m - kPiece] >> dshift) == (K[m] >> dshift);
+}
+
+// The linking table of a wavefront.
+struct PtTable {
+  unsigned long long key[kLkSlots];  // 0: free; the hash that mixes to 0 has slot kLkSlots
+  uint32_t last[kLkSlots + 1], first[kLkSlots + 1], cnt[kLkSlots + 1];
+};
+
+__device__ __forceinline__ void pt_clear(PtTable& T) {
+  __syncthreads();
+  for (uint32_t i = lane_id(); i < kLkSlots; i += 64) {
+    T.key[i] = 0;
+    T.last[i] = kNone;
+  }
+  if (lane_id() == 0) T.last[kLkSlots] = kNone;
+  __syncthreads();
+}
+
+// The slot of the lane's block (`in`), inserted where it is new; the number of
+// new ones.  The caller has checked that the table has room.
+__device__ __forceinline__ uint32_t pt_slot(PtTable& T, uint64_t k, bool in, int sshift,
+                                            uint32_t& fresh_n) {
+  uint32_t s = k == 0ull ? kLkSlots : (uint32_t)(k >> sshift) & (kLkSlots - 1);
+  bool todo = in && k != 0ull, fresh = false;
+  while (__ballot(todo)) {
+    if (todo) {
+      const unsigned long long old = atomicCAS(&T.key[s], 0ull, (unsigned long long)k);
+      fresh = old == 0ull;
+      if (fresh || old == k) todo = false;
+      else s = (s + 1) & (kLkSlots - 1);
+    }
+  }
+  fresh_n = (uint32_t)__popcll(__ballot(fresh));
+  return s;
+}
+
+// Atomics on one address are taken one at a time: only those that may count.
+__device__ __forceinline__ void pt_most(uint32_t most, DevStats* st) {
+  most = wave_max_u32(most);
+  if (lane_id() == 0 &&
+      most > __hip_atomic_load(&st->mult, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
+    atomicMax(&st->mult, (unsigned long long)most);
+}
+
 // Links of the partitioned accesses.  A wavefront takes the stretches (equal
 // top `bits` bits) that start in its `chunk` elements, in order, 64 elements
 // at a time: each finds its block's slot in an LDS hash table, its previous
@@ -343,52 +401,73 @@ __global__ __launch_bounds__(kRsNT) void k_pt_scatter(const uint64_t* __restrict
 // compute unit.  Rows were cut where a stretch ended, and the next one loaded
 // from there; they are now taken whole and loaded two ahead (1.09e8 accesses:
 // 2.03 -> 1.67 ms, 4.6e6: 114 -> 79 us).
+//
+// A block that many requests share makes its stretch as long as its accesses
+// are many, so a stretch is cut at the multiples of kPiece that lie a whole
+// piece and more inside it (a chunk lies between two such multiples).  The
+// wavefront that comes to the first cut ends there; the workgroups from
+// `chunks` on take one piece each, if the stretch is cut at its start.  A part
+// links its own accesses and lists its blocks for k_pt_join.  (One wavefront
+// for a whole stretch: 1e7 accesses, every second one of one block, loaded in
+// 58 ms, now 1.4; 1e8 accesses, one in 75 of one block, 26.7 ms, now 12.6.  Pieces
+// of 4,096 serve the second of these alike, the first in 1.75 ms: more parts to
+// join one after another.)
 __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
                                                 const uint32_t* __restrict__ V, uint32_t n,
-                                                int bits, uint32_t chunk,
-                                                uint2* __restrict__ out, DevStats* st) {
-  __shared__ unsigned long long key[kLkSlots];  // 0: free; the hash that mixes to 0 has slot kLkSlots
-  __shared__ uint32_t last[kLkSlots + 1], first[kLkSlots + 1], cnt[kLkSlots + 1];
+                                                int bits, uint32_t chunk, uint32_t chunks,
+                                                uint2* __restrict__ out, PtLists pl,
+                                                DevStats* st) {
+  __shared__ PtTable T;
   const uint32_t lane = lane_id();
   const uint64_t lt = lanemask_lt();
   const int dshift = 64 - bits, sshift = 64 - bits - kLkBits;
-  const auto clear = [&]() {
-    __syncthreads();
-    for (uint32_t i = lane; i < kLkSlots; i += 64) {
-      key[i] = 0;
-      last[i] = kNone;
-    }
-    if (lane == 0) last[kLkSlots] = kNone;
-    __syncthreads();
-  };
-  clear();
-  const uint32_t c0 = blockIdx.x * chunk, c1 = min(n, c0 + chunk);
-  // the first stretch that starts in the chunk
-  uint32_t at = c0;
-  if (c0) {
-    uint64_t before = K[c0 - 1] >> dshift;
-    for (;;) {
-      const uint32_t i = at + lane;
-      const uint64_t dg = (i < c1 ? K[i] : 0ull) >> dshift;
-      const uint64_t m = __ballot(i < c1 && dg != before);
-      if (m) {
-        at += (uint32_t)__builtin_ctzll(m);
-        break;
+  // the elements [at, stop), less those from the first stretch on that starts
+  // at c1 or later; `part` is the list to write if `stop` is reached, or in any case
+  uint32_t at, c1, stop, part = kNone;
+  const bool piece = blockIdx.x >= chunks;
+  if (piece) {
+    at = (blockIdx.x - chunks + 1) * kPiece;
+    if (!pt_cut(K, n, dshift, at)) return;
+    c1 = at + 1;
+    stop = min(n, at + kPiece);
+    part = at / kPiece;
+  } else {
+    at = blockIdx.x * chunk;
+    c1 = min(n, at + chunk);
+    if (at) {  // the first stretch that starts in the chunk
+      const uint64_t before = K[at - 1] >> dshift;
+      if ((K[c1 - 1] >> dshift) == before) return;
+      for (;;) {
+        const uint32_t i = at + lane;
+        const uint64_t dg = (i < c1 ? K[i] : 0ull) >> dshift;
+        const uint64_t m = __ballot(i < c1 && dg != before);
+        if (m) {
+          at += (uint32_t)__builtin_ctzll(m);
+          break;
+        }
+        at += 64;
       }
-      at += 64;
-      if (at >= c1) return;
     }
+    // the first cut that the last of them may come to
+    stop = (c1 + kPiece - 1) / kPiece * kPiece;
+    if (!pt_cut(K, n, dshift, stop)) {
+      stop += kPiece;
+      if (!pt_cut(K, n, dshift, stop)) stop = n;
+    }
+    if (stop < n) part = stop / kPiece - 1;
   }
+  pt_clear(T);
   // rows of 64, two loaded ahead.  A row is taken whole, whatever stretches it
-  // spans; it is cut only where the table is emptied and where the chunk's
-  // last stretch ends.
+  // spans; it is cut only where the table is emptied and at the end.
   uint32_t occ = 0, most = 0;
   const auto ldk = [&](uint32_t i) { return K[min(i, n - 1)]; };
   const auto ldv = [&](uint32_t i) { return V[min(i, n - 1)]; };
   uint64_t k = ldk(at + lane), k1 = ldk(at + 64 + lane);
   uint32_t v = ldv(at + lane), v1 = ldv(at + 64 + lane);
   uint64_t prev = ~0ull;  // the digit before the row (none yet: no digit has 64 bits)
-  for (; at < n; at += 64) {
+  uint32_t from = at, to = stop;  // the stretch in hand, and the end
+  bool full = false;
+  for (; at < stop; at += 64) {
     const uint32_t i = at + lane;
     const uint64_t k2 = ldk(i + 128);
     const uint32_t v2 = ldv(i + 128);
@@ -398,18 +477,20 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
     uint64_t db = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(dg >> 32), (int)up, 64) << 32) |
                   (uint32_t)__shfl((int)(uint32_t)dg, (int)up, 64);
     if (lane == 0) db = prev;
-    const uint64_t starts = __ballot(i < n && dg != db);
+    const uint64_t starts = __ballot(i < stop && dg != db);
     prev = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(dg >> 32), 63) << 32) |
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)dg, 63);
-    uint64_t row = __ballot(i < n);  // still to be taken
+    uint64_t row = __ballot(i < stop);  // still to be taken
     bool end = false;
     if (at + 64 > c1) {
       const uint64_t out_of = at >= c1 ? starts : starts & (~0ull << (c1 - at));
       if (out_of) {
+        to = at + (uint32_t)__builtin_ctzll(out_of);
         row &= (1ull << __builtin_ctzll(out_of)) - 1;
         end = true;
       }
     }
+    if (starts & row) from = at + 63 - (uint32_t)__builtin_clzll(starts & row);
     while (row) {
       uint64_t mine = row;
       if (occ > kLkClear) {
@@ -417,7 +498,7 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
         if (b) {
           mine = row & ((1ull << __builtin_ctzll(b)) - 1);
           if (!mine) {  // the stretch starts here
-            clear();
+            pt_clear(T);
             occ = 0;
             mine = row;
           }
@@ -426,21 +507,12 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
       row &= ~mine;
       const bool in = (mine >> lane) & 1ull;
       if (occ + 64 > kLkSlots) {  // too many distinct blocks: the load is redone by sorting
-        if (lane == 0) atomicOr(&st->full, 1u);
-        end = true;
+        full = true;
         break;
       }
-      uint32_t s = k == 0ull ? kLkSlots : (uint32_t)(k >> sshift) & (kLkSlots - 1);
-      bool todo = in && k != 0ull, fresh = false;
-      while (__ballot(todo)) {
-        if (todo) {
-          const unsigned long long old = atomicCAS(&key[s], 0ull, (unsigned long long)k);
-          fresh = old == 0ull;
-          if (fresh || old == k) todo = false;
-          else s = (s + 1) & (kLkSlots - 1);
-        }
-      }
-      occ += (uint32_t)__popcll(__ballot(fresh));
+      uint32_t fresh;
+      const uint32_t s = pt_slot(T, k, in, sshift, fresh);
+      occ += fresh;
       uint64_t peers = mine;
 #pragma unroll
       for (int b = 0; b <= kLkBits; ++b) {
@@ -449,7 +521,7 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
         peers &= bit ? bb : ~bb;
       }
       const uint64_t lower = peers & lt;
-      const uint32_t l = in ? last[s] : 0u, f = in ? first[s] : 0u, c = in ? cnt[s] : 0u;
+      const uint32_t l = in ? T.last[s] : 0u, f = in ? T.first[s] : 0u, c = in ? T.cnt[s] : 0u;
       const int pl = lower ? 63 - __builtin_clzll(lower) : 0;
       const int ll = peers ? __builtin_ctzll(peers) : 0;
       const uint32_t vp = (uint32_t)__shfl((int)v, pl, 64), v0 = (uint32_t)__shfl((int)v, ll, 64);
@@ -457,23 +529,151 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
       if (in) out[i] = make_uint2(lower ? vp + 1u : l + 1u, fp);  // kNone + 1 = 0
       if (in && (peers >> lane) == 1ull) {  // the slot's latest element
         const uint32_t tot = (l == kNone ? 0u : c) + (uint32_t)__popcll(peers);
-        last[s] = v;
-        first[s] = fp;
-        cnt[s] = tot;
+        T.last[s] = v;
+        T.first[s] = fp;
+        T.cnt[s] = tot;
         most = max(most, tot);
       }
     }
-    if (end) break;
+    if (end || full) break;
     k = k1;
     v = v1;
     k1 = k2;
     v1 = v2;
   }
-  most = wave_max_u32(most);
-  // atomics on one address are taken one at a time: only those that may count
-  if (lane == 0 &&
-      most > __hip_atomic_load(&st->mult, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-    atomicMax(&st->mult, (unsigned long long)most);
+  if (full && lane == 0) atomicOr(&st->full, 1u);
+  pt_most(most, st);
+  if (full || part == kNone || !(piece || to == stop)) return;
+  // the part's blocks, by their first elements
+  __syncthreads();
+  const uint64_t base = (uint64_t)part * kPiece;
+  uint32_t m = 0;
+  for (uint32_t r = from; r < to; r += 64) {
+    const uint32_t i = r + lane;
+    const bool is = i < to && out[min(i, to - 1)].x == 0u;
+    const uint64_t who = __ballot(is);
+    if (!who) continue;
+    uint32_t fresh;  // none: every block is there
+    const uint32_t s = pt_slot(T, is ? K[i] : 0ull, is, sshift, fresh);
+    if (is) {
+      const uint64_t q = base + m + (uint32_t)__popcll(who & lt);
+      pl.elem[q] = i;
+      pl.last[q] = T.last[s];
+      pl.cnt[q] = T.cnt[s];
+    }
+    m += (uint32_t)__popcll(who);
+  }
+  if (lane == 0) pl.count[part] = m;
+}
+
+// Joins the parts of cut stretches: one wavefront per stretch goes through
+// them in order with the stretch's blocks in a table as above, and gives each
+// block's first access in a part its previous access and the block's first
+// one, out of the parts before.  (The part's other accesses keep that access
+// as their first one: k_names goes on from there.)  Bound by the chain of
+// loads and LDS operations per part, so the lists and what they point to are
+// loaded ahead.  Every wavefront looks at kJoinCuts multiples of kPiece for
+// first cuts of stretches; mostly there are few or none.
+__global__ __launch_bounds__(64) void k_pt_join(const uint64_t* __restrict__ K,
+                                                const uint32_t* __restrict__ V, uint32_t n,
+                                                int bits, uint2* __restrict__ out, PtLists pl,
+                                                DevStats* st) {
+  __shared__ PtTable T;
+  if (st->full) return;
+  const uint32_t lane = lane_id();
+  const int dshift = 64 - bits, sshift = 64 - bits - kLkBits;
+  uint64_t heads;
+  {
+    const uint32_t q = blockIdx.x * kJoinCuts + lane;
+    heads = __ballot(lane < kJoinCuts && pt_cut(K, n, dshift, q * kPiece) &&
+                     !pt_cut(K, n, dshift, (q - 1) * kPiece));
+  }
+  uint32_t most = 0;
+  for (; heads; heads &= heads - 1) {
+    const uint32_t p0 = blockIdx.x * kJoinCuts + (uint32_t)__builtin_ctzll(heads) - 1;
+    const uint64_t dg = K[(uint64_t)(p0 + 1) * kPiece] >> dshift;
+    pt_clear(T);
+    uint32_t occ = 0;
+    // a part's list: its number of blocks (0 past the stretch), and the first
+    // 64 of them; then their hashes and first positions
+    struct List {
+      uint32_t m, elem, last, cnt;
+    };
+    const auto load = [&](uint32_t p) {
+      const uint32_t at = p * kPiece, i = min(at + lane, n - 1);  // (no overflow: n is at most 2^29)
+      const uint64_t kp = K[min(at, n - 1)];
+      List x{pl.count[min(p, (n - 1) / kPiece)], pl.elem[i], pl.last[i], pl.cnt[i]};
+      if (p > p0 && (p > (n - 1) / kPiece || (kp >> dshift) != dg)) x.m = 0;
+      return x;
+    };
+    // groups of kU parts: one in hand, the next one's blocks and the one after's lists under way
+    constexpr int kU = 4;
+    List a[kU], b[kU], c[kU];
+    uint64_t ka[kU], kb[kU];
+    uint32_t va[kU], vb[kU];
+    const auto blocks = [&](const List (&x)[kU], uint64_t (&k)[kU], uint32_t (&v)[kU]) {
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        const uint32_t el = lane < x[u].m ? x[u].elem : 0u;
+        k[u] = K[el];
+        v[u] = V[el];
+      }
+    };
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      a[u] = load(p0 + u);
+      b[u] = load(p0 + kU + u);
+    }
+    blocks(a, ka, va);
+    for (uint32_t p = p0; a[0].m; p += kU) {
+#pragma unroll
+      for (int u = 0; u < kU; ++u) c[u] = load(p + 2 * kU + u);
+      blocks(b, kb, vb);
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        for (uint32_t e = 0; e < a[u].m; e += 64) {
+          const bool in = e + lane < a[u].m;
+          uint32_t el = a[u].elem, last = a[u].last, cnt = a[u].cnt, v = va[u];
+          uint64_t k = ka[u];
+          if (e) {
+            const uint32_t i = (p + u) * kPiece + min(e + lane, a[u].m - 1);
+            el = pl.elem[i];
+            last = pl.last[i];
+            cnt = pl.cnt[i];
+            k = K[el];
+            v = V[el];
+          }
+          if (occ + 64 > kLkSlots) {  // too many distinct blocks: the load is redone by sorting
+            if (lane == 0) atomicOr(&st->full, 1u);
+            return;
+          }
+          uint32_t fresh;
+          const uint32_t s = pt_slot(T, k, in, sshift, fresh);
+          occ += fresh;
+          if (in) {
+            const uint32_t l = T.last[s];
+            if (l == kNone) {
+              T.first[s] = v;
+            } else {
+              out[el] = make_uint2(l + 1u, T.first[s]);
+              cnt += T.cnt[s];
+            }
+            T.last[s] = last;
+            T.cnt[s] = cnt;
+            most = max(most, cnt);
+          }
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < kU; ++u) {
+        a[u] = b[u];
+        b[u] = c[u];
+        ka[u] = kb[u];
+        va[u] = vb[u];
+      }
+    }
+  }
+  pt_most(most, st);
 }
 
 // One partition pass undone: out[i] = in[dst[i]].
@@ -578,6 +778,14 @@ __global__ __launch_bounds__(256) void k_names(const uint32_t* __restrict__ key,
       p[e] = fpre[f[e] >> 6];
       wf[e] = w8[f[e]];
       gf[e] = g8[f[e]];
+    }
+    // the first access of a later part of a cut stretch: on to the block's own
+#pragma unroll
+    for (int e = 0; e < kU; ++e) {
+      if ((m[e] >> (f[e] & 63)) & 1ull) continue;
+      f[e] = fpos[f[e]];
+      m[e] = fbits[f[e] >> 6];
+      p[e] = fpre[f[e] >> 6];
     }
 #pragma unroll
     for (int e = 0; e < kU; ++e) {
@@ -1129,9 +1337,17 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
     // 97, 105 us for 4.6e6, 2.29, 2.03, 1.86, 1.76, 1.67 ms for 1.09e8.
     uint32_t chunk = 256;
     while (chunk < 4096 && n >= (uint64_t)chunk * 16384) chunk *= 2;
-    hipLaunchKernelGGL(k_pt_link, dim3(div_up(n, chunk)), dim3(64), 0, s, K, V, (uint32_t)n, bits,
-                       chunk, links, dstats);
+    // cut stretches' lists, in memory that is written only later
+    const PtLists pl{o.key.as<uint32_t>(), o.nxt.as<uint32_t>(), o.bid.as<uint32_t>(), cnt};
+    const uint32_t chunks = div_up(n, chunk), cuts = ((uint32_t)n - 1) / kPiece;
+    hipLaunchKernelGGL(k_pt_link, dim3(chunks + cuts), dim3(64), 0, s, K, V, (uint32_t)n, bits,
+                       chunk, chunks, links, pl, dstats);
     KV_HIP(hipGetLastError());
+    if (cuts) {
+      hipLaunchKernelGGL(k_pt_join, dim3(cuts / kJoinCuts + 1), dim3(64), 0, s, K, V, (uint32_t)n,
+                         bits, links, pl, dstats);
+      KV_HIP(hipGetLastError());
+    }
     uint32_t* fpos = V;                    // free now, as is K
     uint64_t* fbits;
     if (two) {
