@@ -349,10 +349,18 @@ __device__ __forceinline__ bool pt_cut(const uint64_t* __restrict__ K, uint32_t 
   return m >= kPiece && m < n && (K[m - kPiece] >> dshift) == (K[m] >> dshift);
 }
 
-// The linking table of a wavefront.
+// The linking table of a wavefront: 20,480 bytes, an eighth of a compute
+// unit's LDS.  A free slot's key is 0, so the block whose hash mixes to 0 is
+// kept beside it, in registers that all lanes hold alike.  (With a slot of its
+// own, 20,520 bytes, seven fit: k_pt_link over 1e8 accesses 1.44 ms, now 1.34.)
 struct PtTable {
-  unsigned long long key[kLkSlots];  // 0: free; the hash that mixes to 0 has slot kLkSlots
-  uint32_t last[kLkSlots + 1], first[kLkSlots + 1], cnt[kLkSlots + 1];
+  unsigned long long key[kLkSlots];
+  uint32_t last[kLkSlots], first[kLkSlots], cnt[kLkSlots];
+};
+static_assert(sizeof(PtTable) * 8 == 160 * 1024, "eight wavefronts to a compute unit");
+
+struct PtZero {
+  uint32_t last = kNone, first = 0, cnt = 0;
 };
 
 __device__ __forceinline__ void pt_clear(PtTable& T) {
@@ -361,12 +369,12 @@ __device__ __forceinline__ void pt_clear(PtTable& T) {
     T.key[i] = 0;
     T.last[i] = kNone;
   }
-  if (lane_id() == 0) T.last[kLkSlots] = kNone;
   __syncthreads();
 }
 
-// The slot of the lane's block (`in`), inserted where it is new; the number of
-// new ones.  The caller has checked that the table has room.
+// The slot of the lane's block (`in`), inserted where it is new (kLkSlots for
+// the one that is kept beside the table); the number of new ones.  The caller
+// has checked that the table has room.
 __device__ __forceinline__ uint32_t pt_slot(PtTable& T, uint64_t k, bool in, int sshift,
                                             uint32_t& fresh_n) {
   uint32_t s = k == 0ull ? kLkSlots : (uint32_t)(k >> sshift) & (kLkSlots - 1);
@@ -397,8 +405,8 @@ __device__ __forceinline__ void pt_most(uint32_t most, DevStats* st) {
 // access is the latest lower lane of that slot or the slot's latest position.
 // out[k] = (previous position + 1 or 0, position of the block's first access).
 // The table is emptied between stretches once it fills up; bound by the chain
-// of LDS operations per 64 elements, with eight wavefronts (20 KB each) to a
-// compute unit.  Rows were cut where a stretch ended, and the next one loaded
+// of LDS operations per 64 elements, with eight wavefronts to a compute unit.
+// Rows were cut where a stretch ended, and the next one loaded
 // from there; they are now taken whole and loaded two ahead (1.09e8 accesses:
 // 2.03 -> 1.67 ms, 4.6e6: 114 -> 79 us).
 //
@@ -457,6 +465,7 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
     if (stop < n) part = stop / kPiece - 1;
   }
   pt_clear(T);
+  PtZero z;
   // rows of 64, two loaded ahead.  A row is taken whole, whatever stretches it
   // spans; it is cut only where the table is emptied and at the end.
   uint32_t occ = 0, most = 0;
@@ -521,18 +530,27 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
         peers &= bit ? bb : ~bb;
       }
       const uint64_t lower = peers & lt;
-      const uint32_t l = in ? T.last[s] : 0u, f = in ? T.first[s] : 0u, c = in ? T.cnt[s] : 0u;
+      const bool tab = in && s < kLkSlots;
+      const uint32_t l = tab ? T.last[s] : z.last, f = tab ? T.first[s] : z.first;
+      const uint32_t c = tab ? T.cnt[s] : z.cnt;
       const int pl = lower ? 63 - __builtin_clzll(lower) : 0;
       const int ll = peers ? __builtin_ctzll(peers) : 0;
       const uint32_t vp = (uint32_t)__shfl((int)v, pl, 64), v0 = (uint32_t)__shfl((int)v, ll, 64);
       const uint32_t fp = l == kNone ? v0 : f;
       if (in) out[i] = make_uint2(lower ? vp + 1u : l + 1u, fp);  // kNone + 1 = 0
-      if (in && (peers >> lane) == 1ull) {  // the slot's latest element
-        const uint32_t tot = (l == kNone ? 0u : c) + (uint32_t)__popcll(peers);
+      const bool top = in && (peers >> lane) == 1ull;  // the slot's latest element
+      const uint32_t tot = (l == kNone ? 0u : c) + (uint32_t)__popcll(peers);
+      if (top) most = max(most, tot);
+      if (top && tab) {
         T.last[s] = v;
         T.first[s] = fp;
         T.cnt[s] = tot;
-        most = max(most, tot);
+      }
+      if (const uint64_t m0 = __ballot(top && !tab)) {
+        const int q = __builtin_ctzll(m0);
+        z.last = (uint32_t)__builtin_amdgcn_readlane((int)v, q);
+        z.first = (uint32_t)__builtin_amdgcn_readlane((int)fp, q);
+        z.cnt = (uint32_t)__builtin_amdgcn_readlane((int)tot, q);
       }
     }
     if (end || full) break;
@@ -558,8 +576,8 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
     if (is) {
       const uint64_t q = base + m + (uint32_t)__popcll(who & lt);
       pl.elem[q] = i;
-      pl.last[q] = T.last[s];
-      pl.cnt[q] = T.cnt[s];
+      pl.last[q] = s < kLkSlots ? T.last[s] : z.last;
+      pl.cnt[q] = s < kLkSlots ? T.cnt[s] : z.cnt;
     }
     m += (uint32_t)__popcll(who);
   }
@@ -593,6 +611,7 @@ __global__ __launch_bounds__(64) void k_pt_join(const uint64_t* __restrict__ K,
     const uint32_t p0 = blockIdx.x * kJoinCuts + (uint32_t)__builtin_ctzll(heads) - 1;
     const uint64_t dg = K[(uint64_t)(p0 + 1) * kPiece] >> dshift;
     pt_clear(T);
+    PtZero z;
     uint32_t occ = 0;
     // a part's list: its number of blocks (0 past the stretch), and the first
     // 64 of them; then their hashes and first positions
@@ -650,17 +669,24 @@ __global__ __launch_bounds__(64) void k_pt_join(const uint64_t* __restrict__ K,
           uint32_t fresh;
           const uint32_t s = pt_slot(T, k, in, sshift, fresh);
           occ += fresh;
-          if (in) {
-            const uint32_t l = T.last[s];
-            if (l == kNone) {
-              T.first[s] = v;
-            } else {
-              out[el] = make_uint2(l + 1u, T.first[s]);
-              cnt += T.cnt[s];
-            }
+          const bool tab = in && s < kLkSlots;
+          const uint32_t l = tab ? T.last[s] : z.last;
+          const uint32_t f = l == kNone ? v : tab ? T.first[s] : z.first;
+          if (in && l != kNone) {
+            out[el] = make_uint2(l + 1u, f);
+            cnt += tab ? T.cnt[s] : z.cnt;
+          }
+          if (in) most = max(most, cnt);
+          if (tab) {
             T.last[s] = last;
+            T.first[s] = f;
             T.cnt[s] = cnt;
-            most = max(most, cnt);
+          }
+          if (const uint64_t m0 = __ballot(in && !tab)) {
+            const int q = __builtin_ctzll(m0);
+            z.last = (uint32_t)__builtin_amdgcn_readlane((int)last, q);
+            z.first = (uint32_t)__builtin_amdgcn_readlane((int)f, q);
+            z.cnt = (uint32_t)__builtin_amdgcn_readlane((int)cnt, q);
           }
         }
       }
