@@ -820,10 +820,11 @@ kv_status excl_run(Trace& t, const kv_config* cfg_host, uint32_t n_cfg, const Gr
     KV_HIP(hipGetLastError());
     return KV_OK;
   };
-  const uint32_t err_base = (uint32_t)t.err_jobs.size();
+  const uint32_t err_base = t.err_first + (uint32_t)t.err_jobs.size();
+  const uint32_t job0 = (uint32_t)t.err_jobs.size() - t.err_call;  // after the inclusive replays
   for (uint32_t i = n_lru; i < ns; ++i) {
     const ReplayJob& r = tops[order[i]];
-    t.err_jobs.push_back(ReplayJobInfo{r.policy, r.group, r.cap});
+    t.err_add(r.policy, r.group, r.cap);
   }
   uint32_t w0 = 0;  // the first wave walks the LRU streams too
   t.emit_stage.clear();
@@ -842,7 +843,7 @@ kv_status excl_run(Trace& t, const kv_config* cfg_host, uint32_t n_cfg, const Gr
     if ((st = replay_emit(t, ej, slab, tab + t_jobs + emit_table_bytes() * (lo[v] - n_lru),
                           t.emit_stage,
                           reinterpret_cast<unsigned long long*>(tab + t_jcnt) + 4ull * G * lo[v],
-                          err_base + lo[v] - n_lru, s)) != KV_OK)
+                          err_base + lo[v] - n_lru, job0 + lo[v] - n_lru, s)) != KV_OK)
       return st;
     const uint32_t nj = lo[v + 1] - lo[v];
     const XStream* x = xs_dev + lo[v];

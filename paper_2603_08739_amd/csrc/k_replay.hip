@@ -2302,7 +2302,8 @@ static kv_status aux_stream(AuxStream** out) {
 
 // Test hooks, read at every call: KVCFG_TEST_REPLAY_BUDGET caps the replay
 // state of one wave (bytes), so that a small batch needs several waves;
-// KVCFG_TEST_FAIL_JOB makes that replay job report a failed state check
+// KVCFG_TEST_FAIL_JOB makes that LFU replay job of the call (the top tiers of
+// exclusive hierarchies come behind the others) report a failed state check
 // (its kernel still runs to completion), so that the error path is seen.
 static uint64_t replay_test_budget() {
   const char* e = std::getenv("KVCFG_TEST_REPLAY_BUDGET");
@@ -2361,7 +2362,7 @@ EmitLayout emit_layout(const Trace& t, uint32_t policy, uint64_t n) {
 
 kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab, uint8_t* tables,
                       std::vector<uint8_t>& stage, unsigned long long* jcnt, uint32_t err_base,
-                      hipStream_t s) {
+                      uint32_t first, hipStream_t s) {
   const uint32_t nj = (uint32_t)jobs.size();
   const size_t at = stage.size();
   stage.resize(at + nj * sizeof(JobDev));
@@ -2392,6 +2393,8 @@ kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab,
   a.job_lo = 0;
   a.job_hi = nj;
   a.err_base = err_base;
+  const uint32_t hook = replay_test_fail_job();
+  if (hook != kNone && hook >= first) a.fail_job = hook - first;
   a.emit = reinterpret_cast<uint32_t*>(slab);
   uint64_t* state = reinterpret_cast<uint64_t*>(slab);
   uint32_t* cls = reinterpret_cast<uint32_t*>(slab);
@@ -2625,6 +2628,8 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
                           s));
   JobArgs ja = order_args(t);
   ja.fail_job = replay_test_fail_job();
+  ja.err_base = t.err_first + (uint32_t)t.err_jobs.size();
+  for (const JobDev& j : jd) t.err_add(j.policy, j.group, j.cap);
   const uint32_t nj = (uint32_t)jd.size();
   auto wave_args = [&](uint32_t w) {
     JobArgs x = ja;
@@ -2818,9 +2823,6 @@ kv_status replay_run(Trace& t, const std::vector<ReplayJob>& jobs, const kv_conf
   tm.reset();
   if (any[0] || any[1]) {
     // the LFU jobs' error record, read by the next call on this trace
-    t.err_jobs.resize(jd.size());
-    for (size_t i = 0; i < jd.size(); ++i)
-      t.err_jobs[i] = ReplayJobInfo{jd[i].policy, jd[i].group, jd[i].cap};
     KV_HIP(hipMemcpyAsync(t.err_host, t.err.p, 2 * sizeof(uint32_t), hipMemcpyDeviceToHost, s));
     KV_HIP(hipEventRecord(t.err_pin->ev, s));
     t.err_pending = true;

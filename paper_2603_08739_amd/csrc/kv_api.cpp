@@ -289,12 +289,12 @@ kv_status check_device_error(Trace& t, bool wait, const char* who) {
   if (code == 0) return KV_OK;
   t.err_host[0] = t.err_host[1] = 0;
   KV_HIP(hipMemset(t.err.p, 0, 2 * sizeof(uint32_t)));
-  std::string what = "replay job " + std::to_string(job);
+  std::string what = "a replay job";
   if (code == 2) {
     what = "the exclusive hierarchy of configuration " + std::to_string(job);
-  } else if (job < t.err_jobs.size()) {
-    const ReplayJobInfo& j = t.err_jobs[job];
-    what += std::string(" (") + (j.policy == KV_POLICY_LFU ? "LFU" : "FIFO") + ", capacity " +
+  } else if (job - t.err_first < t.err_jobs.size()) {
+    const ReplayJobInfo& j = t.err_jobs[job - t.err_first];
+    what = "replay job " + std::to_string(j.index) + std::string(" (") + (j.policy == KV_POLICY_LFU ? "LFU" : "FIFO") + ", capacity " +
             std::to_string(j.cap) + " granules, " +
             (j.group == KV_MAX_GROUPS ? std::string("shared") : "group " + std::to_string(j.group)) +
             ")";
@@ -751,6 +751,11 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
   if (!is_live(t)) return fail(KV_ERR_INVALID, "kv_eval_configs: not a live trace handle");
   kv_status st;
   if ((st = check_device_error(*t, false, "kv_eval_configs")) != KV_OK) return st;
+  if (!t->err_pending) {  // the earlier calls' jobs are done with
+    t->err_first += (uint32_t)t->err_jobs.size();
+    t->err_jobs.clear();
+  }
+  t->err_call = (uint32_t)t->err_jobs.size();
   if ((st = validate_model(model)) != KV_OK) return st;
   if (n_cfg == 0) return KV_OK;
   if (!cfg || !counts) return fail(KV_ERR_INVALID, "kv_eval_configs: cfg and counts are required");
@@ -931,7 +936,6 @@ kv_status kv_eval_configs(const kv_trace* h, const kv_config* cfg, uint32_t n_cf
                         counts, store_cg, s);
     return KV_OK;
   };
-  t->err_jobs.clear();
   // ---- FIFO / LFU: replay jobs, with the LRU work running meanwhile
   if (!jobs.empty()) {
     if ((st = replay_run(*t, jobs, cfg, cfg_dev, n_cfg, counts, s, lru)) != KV_OK) return st;

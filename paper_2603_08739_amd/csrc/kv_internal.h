@@ -83,6 +83,7 @@ struct ThresholdSet {
 
 // What an error message needs to name a replay job.
 struct ReplayJobInfo {
+  uint32_t index;  // in its call
   uint32_t policy, group;
   uint64_t cap;
 };
@@ -156,7 +157,17 @@ struct Trace {
   PinBlock* err_pin = nullptr;
   uint32_t* err_host = nullptr;  // in err_pin
   bool err_pending = false;
-  std::vector<ReplayJobInfo> err_jobs;  // the replayed jobs of the latest call
+  // The replayed jobs of the calls whose outcome is not known yet (the latest
+  // call, and those before it that it did not wait for).  Records name a job by
+  // a number that goes on from call to call: err_jobs[i] has err_first + i.
+  std::vector<ReplayJobInfo> err_jobs;
+  uint32_t err_first = 0;
+  uint32_t err_call = 0;  // the latest call's jobs start here in err_jobs
+  // Adds a job of the latest call; its number.
+  uint32_t err_add(uint32_t policy, uint32_t group, uint64_t cap) {
+    err_jobs.push_back(ReplayJobInfo{(uint32_t)err_jobs.size() - err_call, policy, group, cap});
+    return err_first + (uint32_t)err_jobs.size() - 1;
+  }
   ~Trace();
   // host staging of the latest kv_eval_configs call (alive across its copies)
   ThresholdSet shared_ts, part_ts, leaf_ts;
@@ -316,10 +327,11 @@ uint64_t emit_table_bytes();  // device table bytes per job
 // jcnt: [jobs][n_groups][4] insertions, their weight, evictions, their weight
 // (written); tables: device memory for the job table, staged at the end of
 // `stage`, which must not move while the copy is in flight; a job that fails
-// its state check is recorded as err_base + its index.
+// its state check is recorded as err_base + its index.  first: the index of
+// jobs[0] among the replayed jobs of the call (a test hook names jobs by it).
 kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab, uint8_t* tables,
                       std::vector<uint8_t>& stage, unsigned long long* jcnt, uint32_t err_base,
-                      hipStream_t s);
+                      uint32_t first, hipStream_t s);
 
 // exclusive hierarchies without a split stack (k_excl.hip)
 // Whether hierarchy g of C (group g when partitioned, 0 otherwise) is
