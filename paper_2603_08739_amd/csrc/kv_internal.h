@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <string>
+#include <algorithm>
 #include <functional>
 #include <vector>
 
@@ -338,6 +339,13 @@ kv_status replay_emit(Trace& t, const std::vector<EmitJob>& jobs, uint8_t* slab,
 // evaluated there: the exclusive mode under FIFO or LFU, or under LRU when
 // the trace's blocks have mixed weights (otherwise a split stack serves it).
 bool excl_replayed(const kv_config& C, uint32_t g, bool mixed);
+// Most bytes of the buffer the streams of one wave share, `total` for all
+// streams at once, with `free` bytes free on the device and `held` in the
+// buffer already: half of what is free, as the trace keeps the buffer and the
+// caller has work of its own (up to 4 GiB are taken without asking).
+inline uint64_t excl_budget(uint64_t total, uint64_t free, uint64_t held) {
+  return total <= (4ull << 30) ? total : std::min(total, std::max(held, free / 2));
+}
 // Writes the records of every such hierarchy of the batch (the records of a
 // shared hierarchy: every group).  With partitioned configurations over
 // several groups t.part must be built.
