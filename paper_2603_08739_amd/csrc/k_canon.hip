@@ -1161,6 +1161,9 @@ uint32_t grid_of(uint64_t m, uint64_t cap = 32768) {
 // atomics queue on each address.
 constexpr uint64_t kReduceGrid = 1024;
 
+// Unused entries of the block tables from which on they are cut to size.
+constexpr uint64_t kTrimBlocks = 1u << 24;
+
 // Test hooks, read at every load: KVCFG_TEST_LOAD_SORT=1 takes the radix sort;
 // KVCFG_TEST_LOAD_BITS lowers the most partition bits, so that a short trace
 // has long stretches.
@@ -1423,6 +1426,19 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
     return fail(KV_ERR_INVALID, "kv_trace_load: invalid trace:" + why);
   }
   const uint64_t u = hs.u;
+  // the block tables had room for n blocks; kept for the handle's life, they
+  // get what u need where that saves more than the copy's 20 us are worth
+  if (n - u >= kTrimBlocks) {
+    for (DevBuf* b : {&ka, &kb, &va, &vb, &d1, &d2}) b->release();
+    DevBuf own[2];
+    DevBuf* const tab[2] = {&t.blk_w, &t.blk_g};
+    for (int q = 0; q < 2; ++q) {
+      if (own[q].reserve(u) != KV_OK) continue;  // the large table serves as well
+      if ((st = copy_words(tab[q]->p, own[q].p, (u + 15) & ~15ull, s)) != KV_OK) return st;
+      own[q].swap(*tab[q]);
+    }
+    KV_HIP(hipStreamSynchronize(s));  // the large tables go back to the cache
+  }
   kv_trace_stats& ts = t.st;
   ts = kv_trace_stats{};
   ts.n = n;

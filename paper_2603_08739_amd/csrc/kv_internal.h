@@ -41,6 +41,12 @@ struct DevBuf {
   DevBuf& operator=(const DevBuf&) = delete;
   ~DevBuf() { release(); }
   void release();
+  void swap(DevBuf& o) {
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
+    std::swap(cap_bytes, o.cap_bytes);
+    std::swap(dev, o.dev);
+  }
   // Grow to at least `b` bytes (contents are not preserved on growth).
   kv_status reserve(size_t b);
   template <class T>
