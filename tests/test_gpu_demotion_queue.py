@@ -1,6 +1,7 @@
 """Exclusive hierarchies walked as one demotion queue: trace lengths next to
-the walk's steps of 64 events, staged slices of 1,024 events and windows of
-512 entries, capacities from one block (a head passes entries that the same
+the walk's 64 lanes, steps of 256 events, staged slices of 2,048 events (and
+where the last step before a new slice begins) and windows of 1,024 entries
+(events are accesses for LRU over mixed weights), capacities from one block (a head passes entries that the same
 step takes out) to all but one block, every policy, one to three live tiers,
 shared and partitioned, one and more groups, against the oracle (exact)."""
 import numpy as np
@@ -27,7 +28,8 @@ def batch(caps, groups):
     return tg.from_list(items)
 
 
-@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 1023, 1024, 1025, 1600, 4097])
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 127, 255, 256, 257, 511, 513, 1023, 1024, 1025, 1600, 2047, 2048, 2049, 2303, 2305,
+                               4097])
 @pytest.mark.parametrize("groups,weights", [(1, (1,)), (1, (1, 4)), (2, (1, 2, 3))])
 def test_step_edges(oracle_mod, n, groups, weights):
     t = tg.random_trace(n + 7 * groups, n, max(2, n // 5), n_groups=groups, weight_choices=weights, zipf_s=0.5,
