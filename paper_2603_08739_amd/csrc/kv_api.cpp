@@ -513,13 +513,17 @@ struct Piece {
 };
 
 // Copies tables to the device, one after another (each on a multiple of 256
-// bytes): through pinned memory that a kernel reads, or, past kUploadPin
-// bytes and while the stream is captured (a graph reads the host memory again
-// each time it runs), by one copy from `stage`, memory of the trace.  The
-// pieces may be changed once the call returns.
-// Pageable copies of a few KB, up to five in a call, kept the host waiting:
-// its part of a small batch's call took 86 us, now 53 (search batches 97 -> 40).
-constexpr uint64_t kUploadPin = 1u << 20;
+// bytes): from kUploadPage to kUploadPin bytes through pinned memory that a
+// kernel reads; else, and while the stream is captured (a graph reads the host
+// memory again each time it runs), by one copy from `stage`, memory of the
+// trace, which the runtime has read when it returns.  The pieces may be changed
+// once the call returns.
+// What kept the host waiting was up to five copies in a call: its part of a
+// small batch's call took 86 us, now 45.  One copy of a few KB is cheaper than
+// the kernel, its pinned block and event (one TTL 33 and 37 us a call, 25
+// capacities 43 and 46 us of the host), and dearer from some 30 KB on (200
+// capacities 54 and 49 us of the host, 1,000 78 and 70).
+constexpr uint64_t kUploadPage = 20u << 10, kUploadPin = 1u << 20;
 
 kv_status upload(std::vector<uint8_t>& stage, uint8_t* dst, const std::vector<Piece>& pieces,
                  hipStream_t s) {
@@ -532,7 +536,7 @@ kv_status upload(std::vector<uint8_t>& stage, uint8_t* dst, const std::vector<Pi
     (void)hipGetLastError();  // (the legacy stream beside another's capture)
     cap = hipStreamCaptureStatusActive;
   }
-  if (bytes <= kUploadPin && cap == hipStreamCaptureStatusNone) {
+  if (bytes > kUploadPage && bytes <= kUploadPin && cap == hipStreamCaptureStatusNone) {
     if (kv_status st = pin_take(bytes, &pin)) return st;
     host = pin->host;
   } else {

@@ -1,5 +1,5 @@
 """A call's tables on their way to the device: batches below and above the
-size that goes through pinned memory, several in flight on one trace, and
+sizes that go through pinned memory, several in flight on one trace, and
 threads with a trace and a stream each, all against the oracle."""
 import threading
 
@@ -11,7 +11,7 @@ import tracegen as tg
 from paper_2603_08739_amd import host, kvcfg
 
 pytestmark = pytest.mark.gpu
-PIN = (1 << 20) // 560  # configurations of the largest batch through pinned memory
+PIN = (1 << 20) // 560  # configurations of the largest batch through pinned memory (the smallest: 34 or so)
 
 
 def batch(n, seed):
@@ -36,7 +36,7 @@ def in_flight(h, batches, stream=None):
     return [o.cpu().numpy().view(np.uint64) for o in outs]
 
 
-@pytest.mark.parametrize("n", [1, 7, PIN - 40, PIN + 40])
+@pytest.mark.parametrize("n", [1, 7, 30, 36, 40, PIN - 40, PIN + 40])
 def test_calls_in_flight(oracle_mod, n):
     t = trace(n)
     h = host.load(t)
