@@ -43,9 +43,13 @@ constexpr uint32_t kTtlBins = 4096;  // groups * (TTL values + 1)
 // and two LDS atomics serve all of them (per access they were most of the
 // time, the atomics on few addresses taken one lane at a time); what four
 // triples do not cover goes lane by lane.  1e8 accesses, 64 TTLs: 809 -> 286 us
-// (3.5 TB/s of the 10 bytes per access that have to be read).  Without any
-// such neighbours (one access per request, random blocks) nothing is lost:
-// 2e7 accesses 691 -> 651 us.
+// (3.5 TB/s of the 10 bytes per access that have to be read).  A wavefront
+// most of whose threads have kTtlMany runs or more joins no lanes and takes its
+// runs side by side, so that their loads and searches overlap: neighbours are
+// strangers there, and run by run they cost more than they save (1e7 random
+// accesses, 8 TTLs: 160 us, 149 without any joining, now @T; 500 accesses 8.6,
+// 4.3 and @U us).
+constexpr int kTtlMany = 4;
 __global__ __launch_bounds__(kTtlNT) void k_ttl_hist(
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ req,
     const double* __restrict__ rt, const uint8_t* __restrict__ w8,
@@ -98,6 +102,21 @@ __global__ __launch_bounds__(kTtlNT) void k_ttl_hist(
       const int v = u + 1 < kTtlU ? u + 1 : u;
       const bool same = u + 1 < kTtlU && k[v] && r[v] == r[u] && rp[v] == rp[u] && g[v] == g[u];
       ends |= (k[u] && !same ? 1u : 0u) << u;
+    }
+    if (__ballot(__popc(ends) >= kTtlMany)) {
+      uint32_t before = 0;
+#pragma unroll
+      for (int u = 0; u < kTtlU; ++u) {
+        if (!((ends >> u) & 1u)) continue;
+        const uint32_t c = cum[u] - before, wt = c & 0xFFFFu;
+        before = cum[u];
+        const double delta = rt[r[u]] - rt[rp[u]];
+        const uint32_t b = lower_bound(tt, 0u, n_ttl, delta);
+        const uint32_t idx = g[u] * nb + b;
+        atomicAdd(&hcw[idx], (unsigned long long)(c >> 16) << 32 | wt);
+        atomicAdd(&hd[idx], (double)wt * delta);
+      }
+      continue;
     }
     uint32_t done = 0;
     while (__ballot(ends != 0u)) {
