@@ -44,11 +44,11 @@ constexpr uint32_t kTtlBins = 4096;  // groups * (TTL values + 1)
 // time, the atomics on few addresses taken one lane at a time); what four
 // triples do not cover goes lane by lane.  1e8 accesses, 64 TTLs: 809 -> 286 us
 // (3.5 TB/s of the 10 bytes per access that have to be read).  A wavefront
-// most of whose threads have kTtlMany runs or more joins no lanes and takes its
-// runs side by side, so that their loads and searches overlap: neighbours are
-// strangers there, and run by run they cost more than they save (1e7 random
-// accesses, 8 TTLs: 160 us, 149 without any joining, now @T; 500 accesses 8.6,
-// 4.3 and @U us).
+// with a thread of kTtlMany runs or more joins no lanes and takes its runs side
+// by side, so that their loads and searches overlap: neighbours are strangers
+// there, and run after run they cost more than they save (1e7 random accesses,
+// 8 TTLs: 160 us, 149 without any joining, now 150; 500 accesses 8.6, 4.3 and
+// 4.0 us; 1e6 accesses whose group changes at every block 16, 10.5 and 10.6).
 constexpr int kTtlMany = 4;
 __global__ __launch_bounds__(kTtlNT) void k_ttl_hist(
     const uint32_t* __restrict__ key, const uint32_t* __restrict__ req,
