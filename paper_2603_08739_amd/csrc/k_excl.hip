@@ -55,6 +55,8 @@ constexpr uint32_t kXStep = kXNT * kXIt;
 constexpr uint32_t kXStage = 2048; // events staged in LDS at a time
 constexpr uint32_t kXWin = 1024;   // queue entries staged in LDS per tier
 constexpr uint32_t kXBatch = 16;   // loads of one array in flight per lane
+constexpr uint32_t kXShort = 4;    // a step of fewer events is not worth its chain
+constexpr uint32_t kXBurst = 64;   // most events taken one by one in a row
 static_assert(kXStage % (64 * kXBatch) == 0, "slices are staged in whole batches");
 constexpr int kXPrep = 1024;       // threads of the per-stream scans
 
@@ -261,10 +263,20 @@ __device__ __forceinline__ uint32_t step_scan(const uint32_t (&v)[kXIt], uint32_
 // the shortest stretch from the head that weighs as much.  What leaves a tier
 // arrives in the next.  This holds as long as no event of the step takes out
 // an entry that a head passes in the same step; the events before the first
-// such event are taken alone, and that event then makes a step of its own,
-// where its entry counts as taken out.  Heads stand far behind the entries in
-// use unless a tier is small, so steps are nearly always whole (638 steps for
-// 160,001 accesses at the smallest capacities of a weighted mix).
+// such event are taken alone, and that event by itself.  Heads stand far
+// behind the entries in use unless a tier is small, so steps are nearly always
+// whole (638 steps for 160,001 accesses at the smallest capacities of a
+// weighted mix).
+//
+// Where blocks come back within the few entries of small tiers, that event
+// comes after a few others time and again.  Then events are taken one by one,
+// the lanes searching a tier's next 64 entries: one at first, and up to
+// kXBurst in a row while steps stay under kXShort events.  An event by itself
+// takes a microsecond; a step takes two, whatever its length, and a short one
+// up to three tries (500 accesses to 125 blocks, tiers of 4 to 40 granules: 1.4
+// to 1.6 ms with a step for every such event, 0.65 to 0.95 with lists replayed
+// access by access, now 0.55 to 1.05; kXShort = 12 doubled the time of some
+// hierarchies that steps of 5 to 10 events serve well).
 //
 // Bound by the wavefront's dependent chain per step (a few scans and LDS
 // round trips per tier), so a lane takes four events; the events and queue
@@ -272,8 +284,9 @@ __device__ __forceinline__ uint32_t step_scan(const uint32_t (&v)[kXIt], uint32_
 // (one load at a time: 3.8 ms instead of 2.0 ms for the walks below; one
 // event per lane: 6.6 ms).  Measured: 64 FIFO and LFU hierarchies over
 // 238,313 accesses of unit weight walk in 2.0 ms, 48 of every policy over
-// 160,001 accesses of weights 1 and 4 in 4.2 ms; whole evaluations 393 ->
-// 3.7 ms and 464 -> 6.4 ms (lists replayed access by access, before).
+// 160,001 accesses of weights 1 and 4 in 4.2 ms; whole evaluations 355 ->
+// 3.6 ms and 460 -> 6.7 ms (lists replayed access by access, before; the
+// second 6.2 to 9.6 ms by the trace).
 // wu: the weight of every block, or 0 when weights differ.
 template <bool kOne>
 __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, uint32_t g0,
@@ -282,15 +295,100 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
   const uint32_t n_ev = x.meta ? x.meta[0] : x.n, n_en = x.meta ? x.meta[1] : x.n;
   const uint32_t nt = j.nt;
   uint32_t H[KV_TIERS] = {0, 0, 0}, room[KV_TIERS], wb[KV_TIERS];
-  unsigned long long hc[KV_TIERS] = {0, 0, 0}, hw[KV_TIERS] = {0, 0, 0};
-  unsigned long long ec[KV_TIERS] = {0, 0, 0}, ew[KV_TIERS] = {0, 0, 0};
+  // hits and departures: each lane's number, all lanes' weight (no sum of
+  // weights reaches 2^32)
+  uint32_t hc[KV_TIERS] = {0, 0, 0}, hw[KV_TIERS] = {0, 0, 0};
+  uint32_t ec[KV_TIERS] = {0, 0, 0}, ew[KV_TIERS] = {0, 0, 0};
 #pragma unroll
   for (uint32_t t = 0; t < KV_TIERS; ++t) {
     room[t] = j.cap[t];
     wb[t] = kNone;  // no window staged
   }
-  uint32_t send = 0, sbase = 0, ptb = 0, step = kXStep;
-  for (uint32_t k0 = 0; k0 < n_ev;) {
+  uint32_t send = 0, sbase = 0, ptb = 0, step = kXStep, burst = 0, k0 = 0;
+  // stages tier t's window of the queue, from entry `base` on
+  const auto window = [&](uint32_t t, uint32_t base) {
+    __syncthreads();
+    uint32_t so[kXWin / 64], sq[kXWin / 64];
+#pragma unroll
+    for (uint32_t r = 0; r < kXWin / 64; ++r) {
+      const uint32_t q = min(base + lane + 64 * r, n_en - 1);
+      so[r] = x.out[x.base + q];
+      sq[r] = x.qw[x.base + q];
+    }
+#pragma unroll
+    for (uint32_t r = 0; r < kXWin / 64; ++r) {
+      const bool is = base + lane + 64 * r < n_en;  // past the queue: no weight
+      S.out[t][lane + 64 * r] = so[r] == kNone ? kNone : so[r] - x.base;
+      S.qw[t][lane + 64 * r] = is ? (uint8_t)sq[r] : (uint8_t)0;
+    }
+    __syncthreads();
+  };
+  // takes staged events one by one up to `end`; false if the queue ends before
+  // what a tier must let go
+  const auto one_by_one = [&](uint32_t end) -> bool {
+    for (; k0 < end; ++k0) {
+      const uint32_t at = k0 - sbase;
+      const uint32_t e = lane_u32(S.e[at], 0), w = lane_u32(S.w[at], 0);
+      uint32_t arr = w;
+      if (x.pt) {
+        const uint32_t p = lane_u32(S.pt[at], 0);
+        arr = p - ptb;
+        ptb = p;
+      }
+      uint32_t d = nt;  // the tier that holds the event's entry
+#pragma unroll
+      for (int t = KV_TIERS - 1; t >= 0; --t)
+        if ((uint32_t)t < nt && e > H[t]) d = (uint32_t)t;
+      if (!kOne && d < nt && lane == 0) {
+        const uint32_t g = S.g[at];
+        atomicAdd(&S.hit[g][d][0], 1ull);
+        atomicAdd(&S.hit[g][d][1], (unsigned long long)w);
+      }
+#pragma unroll
+      for (uint32_t t = 0; t < KV_TIERS; ++t) {
+        if (t >= nt) continue;
+        if (d == t) {
+          room[t] += w;
+          if (kOne) {
+            hc[t] += lane == 0 ? 1u : 0u;
+            hw[t] += w;
+          }
+        }
+        uint32_t gone = 0;
+        const int32_t over = (int32_t)arr - (int32_t)min(room[t], 1u << 30);
+        while (over > 0 && gone < (uint32_t)over) {
+          const uint32_t base = H[t];
+          if (base >= n_en) return false;
+          if (base < wb[t] || base + 64 > wb[t] + kXWin) {
+            wb[t] = base;
+            window(t, base);
+          }
+          const uint32_t i = base - wb[t] + lane;
+          // alive unless taken out by now, this event's own entry among them
+          const uint32_t v = S.out[t][i] > k0 ? (uint32_t)S.qw[t][i] : 0u;
+          const uint32_t pre = gone + wave_incl_scan_u32(v);
+          const uint64_t enough = __ballot(pre >= (uint32_t)over);
+          const uint32_t l = enough ? (uint32_t)__builtin_ctzll(enough) : 63u;
+          const bool goes = v != 0u && lane <= l;
+          const uint32_t upto = lane_u32(pre, l);
+          if (kOne) {
+            ec[t] += goes ? 1u : 0u;
+            ew[t] += upto - gone;
+          } else if (goes) {
+            const uint32_t g = x.qg[x.base + base + lane];
+            atomicAdd(&S.ev[g][t][0], 1ull);
+            atomicAdd(&S.ev[g][t][1], (unsigned long long)v);
+          }
+          gone = upto;
+          H[t] = base + l + 1;
+        }
+        room[t] += gone - arr;
+        arr = gone;
+      }
+    }
+    return true;
+  };
+  while (k0 < n_ev) {
     if (k0 + kXStep > send && send < n_ev) {
       // stage the next events (the previous ones are read already)
       sbase = k0;
@@ -318,6 +416,14 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
       }
       __syncthreads();
     }
+    if (step < kXShort) {  // (burst is set: only a short clash makes steps short)
+      if (!one_by_one(min(min(n_ev, send), k0 + burst))) {
+        bad = true;
+        return;
+      }
+      step = min(kXStep, burst * 16);
+      continue;
+    }
     const uint32_t m = min(step, n_ev - k0);
     const uint32_t i0 = lane * kXIt, at = k0 - sbase + i0;
     bool in[kXIt];
@@ -338,9 +444,8 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
     uint32_t total;
     if (x.pt) total = S.pt[k0 - sbase + m - 1] - ptb;
     else total = step_scan(w, arr);
-    // an entry is alive for the step unless taken out before its first event;
-    // a step of one event has taken out its own
-    const uint32_t alive = m == 1 ? k0 + 1 : k0;
+    // an entry is alive for the step unless taken out before its first event
+    const uint32_t alive = k0;
     uint32_t clash = kXIt;  // the lane's first event that takes out a passed entry
     uint32_t newH[KV_TIERS], nc[KV_TIERS], nR[KV_TIERS], nA[KV_TIERS], nP[KV_TIERS];
 #pragma unroll
@@ -390,24 +495,8 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
             return;
           }
           if (base < wb[t] || base + kXStep > wb[t] + kXWin) {
-            __syncthreads();
             wb[t] = base;
-            {
-              uint32_t so[kXWin / 64], sq[kXWin / 64];
-#pragma unroll
-              for (uint32_t r = 0; r < kXWin / 64; ++r) {
-                const uint32_t q = min(base + lane + 64 * r, n_en - 1);
-                so[r] = x.out[x.base + q];
-                sq[r] = x.qw[x.base + q];
-              }
-#pragma unroll
-              for (uint32_t r = 0; r < kXWin / 64; ++r) {
-                const bool is = base + lane + 64 * r < n_en;  // past the queue: no weight
-                S.out[t][lane + 64 * r] = so[r] == kNone ? kNone : so[r] - x.base;
-                S.qw[t][lane + 64 * r] = is ? (uint8_t)sq[r] : (uint8_t)0;
-              }
-            }
-            __syncthreads();
+            window(t, base);
           }
           uint32_t qw[kXIt], pre[kXIt];
 #pragma unroll
@@ -443,7 +532,7 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
           uint32_t n_go = 0;  // entries before the lane's first one past the stretch
 #pragma unroll
           for (uint32_t r = 0; r < kXIt; ++r) {
-            nc[t] += (uint32_t)__popcll(__ballot(qw[r] != 0u && pre[r] - qw[r] < most));
+            nc[t] += qw[r] != 0u && pre[r] - qw[r] < most ? 1u : 0u;
             n_go += pre[r] < most ? 1u : 0u;
           }
           if (most <= tot) {
@@ -466,13 +555,11 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
 #pragma unroll
       for (uint32_t r = 0; r < kXIt; ++r) arr[r] = gone[r];
     }
-    if (m > 1) {
-      const uint64_t c = __ballot(clash < kXIt);
-      if (c) {
-        const uint32_t l = (uint32_t)__ffsll((long long)c) - 1u;
-        step = max(1u, l * kXIt + lane_u32(clash, l));
-        continue;
-      }
+    if (const uint64_t c = __ballot(clash < kXIt)) {
+      const uint32_t l = (uint32_t)__ffsll((long long)c) - 1u;
+      step = l * kXIt + lane_u32(clash, l);
+      if (step < kXShort) burst = burst ? min(kXBurst, burst * 4) : 1u;
+      continue;
     }
     // the step stands
 #pragma unroll
@@ -480,7 +567,7 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
       if (t >= nt) continue;
       if (kOne) {
 #pragma unroll
-        for (uint32_t r = 0; r < kXIt; ++r) hc[t] += (uint32_t)__popcll(__ballot(d[r] == t));
+        for (uint32_t r = 0; r < kXIt; ++r) hc[t] += d[r] == t ? 1u : 0u;
         hw[t] += nR[t];
         ec[t] += nc[t];
         ew[t] += nP[t];
@@ -509,13 +596,16 @@ __device__ void walk(const XStream& x, const XWalk& j, uint32_t wu, WalkLds& S, 
     if (x.pt) ptb += nA[0];
     k0 += m;
     step = min(kXStep, m * 16);
+    if (m >= kXShort) burst = 0;
   }
-  if (kOne && lane == 0) {
+  if (kOne) {
 #pragma unroll
     for (uint32_t t = 0; t < KV_TIERS; ++t) {
-      S.hit[g0][t][0] = hc[t];
+      const uint32_t h = wave_sum(hc[t]), v = wave_sum(ec[t]);
+      if (lane != 0) continue;
+      S.hit[g0][t][0] = h;
       S.hit[g0][t][1] = hw[t];
-      S.ev[g0][t][0] = ec[t];
+      S.ev[g0][t][0] = v;
       S.ev[g0][t][1] = ew[t];
     }
   }

@@ -49,3 +49,21 @@ def test_scans_and_cycles(oracle_mod):
         tot = int(np.resize(np.asarray(w), period).sum())
         caps = [(tot - d, max(w) * k, 0) for d in (1, max(w), tot // 2) for k in (1, 2, 9)] + [(tot // 3, tot // 3, tot // 3)]
         compare(oracle_mod, t, batch(caps, 1), f"cycle{period}")
+
+
+@pytest.mark.parametrize("u,n", [(3, 700), (12, 2500), (60, 5000), (125, 2049)])
+@pytest.mark.parametrize("groups,weights", [(1, (1,)), (1, (1, 4)), (2, (1, 2, 3))])
+def test_short_recurrences(oracle_mod, u, n, groups, weights):
+    """Blocks that come back within the few entries of small tiers, now and
+    then or all the time: stretches walked event by event, and long steps
+    between them."""
+    w = max(weights)
+    rng = np.random.default_rng([u, n, groups])
+    hot = rng.integers(0, u, n)
+    calm = np.where(np.arange(n) // 300 % 2, hot, u + np.arange(n) % 700)  # 300 of each in turn
+    for kind, lab in (("hot", hot), ("calm", calm)):
+        ids = np.unique(lab)
+        t = tg.from_blocks(lab, weights={int(b): weights[int(b) % len(weights)] for b in ids},
+                           groups={int(b): int(b) % groups for b in ids}, n_groups=groups, per_request=9)
+        caps = [(w, w, w), (w, 3 * w, 9 * w), (2 * w, 0, 5 * w), (u // 4 + w, u // 4 + w, u // 4 + w), (0, w, u // 2 + w), (u // 2 + w, w, 4 * w)]
+        compare(oracle_mod, t, batch(caps, groups), f"{kind}-u{u}-n{n}-g{groups}-w{weights}")
