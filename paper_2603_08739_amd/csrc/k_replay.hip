@@ -806,16 +806,9 @@ __device__ __forceinline__ int lfu_serial_wave(const JobDev& j, const JobArgs& a
           uint32_t q = i, nq = kNone, vw = 0, vg = 0;
           if (fmin < kTopClass) {
             const uint32_t h0 = fmin == 1 ? head1 : (fmin < kHeadLds ? S.shead[fmin] : head[fmin]);
-            for (uint32_t base = h0; base < i; base += 64) {
-              if (base - h0 >= kFarSearch && base < p0) {  // none of the class before base
-                if (lane == 0) {
-                  S.si = i;
-                  S.sfrom = base;
-                  S.sword = word;
-                }
-                ok = kSerialSearch;
-                break;
-              }
+            // as far as kFarSearch positions, unless p0 comes before
+            const uint32_t stop = p0 > h0 && p0 - h0 > kFarSearch ? h0 + kFarSearch : i;
+            for (uint32_t base = h0; base < stop; base += 64) {
               const uint32_t r = base + lane;
               uint32_t c = 0, nr = kNone, wr = 0, gr = 0;
               if (r < i) {
@@ -841,6 +834,15 @@ __device__ __forceinline__ int lfu_serial_wave(const JobDev& j, const JobArgs& a
                 break;
               }
             }
+            if (q >= i && stop < i) {  // none of the class before `stop`
+              if (lane == 0) {
+                S.si = i;
+                S.sfrom = stop;
+                S.sword = word;
+              }
+              ok = kSerialSearch;
+              break;
+            }
           } else {
             uint64_t best = ~0ull;  // count << 32 | position
             for (uint32_t r = b0 + lane; r < i; r += 64) {
@@ -859,7 +861,6 @@ __device__ __forceinline__ int lfu_serial_wave(const JobDev& j, const JobArgs& a
               vg = q >= p0 ? S.sg[q - p0] : a.g8[o][q];
             }
           }
-          if (ok == kSerialSearch) break;
           if (q >= i) {
             ok = kSerialBad;
             break;
