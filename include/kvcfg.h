@@ -347,9 +347,15 @@ const char* kv_last_error(void);
  * the recorded events and returns, per stage, the number of launches and the
  * summed device milliseconds between each pair.  Process-wide; not meant for
  * concurrent callers.  Stages:
- *   0 load: validation        1 load: radix sort       2 load: links and ids
- *   3 group-partitioned order 4 stack: block matrix    5 stack: in-block sort
- *   6 stack: assembly, bins   7 stack: final depths    8 LRU records
+ *   0 load: checks, copies, statistics, the first partition digit's counts
+ *   1 load: partition (and the radix sort, where a load needs that instead)
+ *   2 load: links and ids
+ *   3 group-partitioned order
+ *   4 stack: block matrix, last-occurrence weights, clearing
+ *   5 stack: in-block sort
+ *   6 stack: distances, final depths and gaps binned, prefix reuse
+ *   7 stack: histograms made cumulative
+ *   8 LRU records
  *   9 replay: job setup       10 replay: LFU jobs      11 replay: combine
  *   12 objectives             13 Pareto filter         14 replay: FIFO jobs
  *   15 TTL curves             16 replay: exclusive hierarchies

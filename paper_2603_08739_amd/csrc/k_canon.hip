@@ -10,7 +10,8 @@
 // (one or two passes), so that a few hundred consecutive ones share all the
 // accesses of their blocks.  A wavefront then takes such a stretch in order,
 // 64 accesses at a time, through a hash table in LDS that holds each block's
-// first and latest position.  Each pass also records where every element
+// first and latest position; a stretch that a much-read block makes long is cut
+// into parts, which are joined afterwards.  Each pass also records where every element
 // went, so the results come back to trace order by gathers whose sources are
 // runs of a tile, not by scattering records to random positions.  Links to the
 // next access and dense ids follow in trace order, where consecutive accesses
@@ -49,6 +50,7 @@ constexpr uint32_t kLkSlots = 1u << kLkBits;
 constexpr uint32_t kLkClear = kLkSlots / 4 - 64;
 constexpr uint32_t kPiece = 8192;                // a long stretch is cut at multiples of this
 constexpr uint32_t kJoinCuts = 16;               // such multiples a joining wavefront looks at
+constexpr uint32_t kCutFrom = 1u << 14;          // traces of more accesses have stretches cut
 
 enum : uint32_t {
   kErrGroup = 1u,
@@ -345,7 +347,7 @@ struct PtLists {
 };
 
 // Whether a stretch is cut at m, a multiple of kPiece: it reaches back a whole
-// piece and more (equal top bits are consecutive).
+// piece and more (equal top bits are consecutive).  n: 0 if none is cut.
 __device__ __forceinline__ bool pt_cut(const uint64_t* __restrict__ K, uint32_t n, int dshift,
                                        uint32_t m) {
   return m >= kPiece && m < n && (K[m - kPiece] >> dshift) == (K[m] >> dshift);
@@ -424,9 +426,9 @@ __device__ __forceinline__ void pt_most(uint32_t most, DevStats* st) {
 // join one after another.)
 __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
                                                 const uint32_t* __restrict__ V, uint32_t n,
-                                                int bits, uint32_t chunk, uint32_t chunks,
-                                                uint2* __restrict__ out, PtLists pl,
-                                                DevStats* st) {
+                                                uint32_t cut_n, int bits, uint32_t chunk,
+                                                uint32_t chunks, uint2* __restrict__ out,
+                                                PtLists pl, DevStats* st) {
   __shared__ PtTable T;
   const uint32_t lane = lane_id();
   const uint64_t lt = lanemask_lt();
@@ -437,7 +439,7 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
   const bool piece = blockIdx.x >= chunks;
   if (piece) {
     at = (blockIdx.x - chunks + 1) * kPiece;
-    if (!pt_cut(K, n, dshift, at)) return;
+    if (!pt_cut(K, cut_n, dshift, at)) return;
     c1 = at + 1;
     stop = min(n, at + kPiece);
     part = at / kPiece;
@@ -460,9 +462,9 @@ __global__ __launch_bounds__(64) void k_pt_link(const uint64_t* __restrict__ K,
     }
     // the first cut that the last of them may come to
     stop = (c1 + kPiece - 1) / kPiece * kPiece;
-    if (!pt_cut(K, n, dshift, stop)) {
+    if (!pt_cut(K, cut_n, dshift, stop)) {
       stop += kPiece;
-      if (!pt_cut(K, n, dshift, stop)) stop = n;
+      if (!pt_cut(K, cut_n, dshift, stop)) stop = n;
     }
     if (stop < n) part = stop / kPiece - 1;
   }
@@ -1166,7 +1168,7 @@ constexpr uint64_t kTrimBlocks = 1u << 24;
 
 // Test hooks, read at every load: KVCFG_TEST_LOAD_SORT=1 takes the radix sort;
 // KVCFG_TEST_LOAD_BITS lowers the most partition bits, so that a short trace
-// has long stretches.
+// has long stretches, and has them cut.
 bool sort_forced() {
   const char* e = std::getenv("KVCFG_TEST_LOAD_SORT");
   return e && e[0] == '1';
@@ -1371,9 +1373,12 @@ kv_status canon_build(Trace& t, const kv_trace_desc& d, hipStream_t s) {
     while (chunk < 4096 && n >= (uint64_t)chunk * 16384) chunk *= 2;
     // cut stretches' lists, in memory that is written only later
     const PtLists pl{o.key.as<uint32_t>(), o.nxt.as<uint32_t>(), o.bid.as<uint32_t>(), cnt};
-    const uint32_t chunks = div_up(n, chunk), cuts = ((uint32_t)n - 1) / kPiece;
-    hipLaunchKernelGGL(k_pt_link, dim3(chunks + cuts), dim3(64), 0, s, K, V, (uint32_t)n, bits,
-                       chunk, chunks, links, pl, dstats);
+    // (one block's 2^14 accesses take one wavefront 0.23 ms, 2^16 0.9 ms; to look
+    // for cuts costs each load 5 us)
+    const bool cut = n > kCutFrom || most_bits() < 2 * kPtBits;
+    const uint32_t chunks = div_up(n, chunk), cuts = cut ? ((uint32_t)n - 1) / kPiece : 0;
+    hipLaunchKernelGGL(k_pt_link, dim3(chunks + cuts), dim3(64), 0, s, K, V, (uint32_t)n,
+                       cut ? (uint32_t)n : 0u, bits, chunk, chunks, links, pl, dstats);
     KV_HIP(hipGetLastError());
     if (cuts) {
       hipLaunchKernelGGL(k_pt_join, dim3(cuts / kJoinCuts + 1), dim3(64), 0, s, K, V, (uint32_t)n,
